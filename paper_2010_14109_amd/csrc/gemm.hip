@@ -1,14 +1,24 @@
-// Dense and convolution layers as one fp32 MFMA GEMM kernel (gfx950).
+// Dense and convolution layers as one MFMA GEMM kernel on fp32 operands (gfx950).
 //
-// C[M][N] = sum_k A[m][k] B[k][n].  A 256-thread workgroup computes a
-// 128 x 128 tile of C (or 128 x 64 / 64 x 128 when one side is at most 64
-// wide); each of its four wave64s owns a quarter of the tile made of
-// v_mfma_f32_32x32x2f32 blocks (2 x 2 of them for 128 x 128).  K is walked in tiles of 32,
-// double-buffered through LDS: while the waves multiply tile t out of one
-// buffer, every thread has tile t+1 in flight from global memory into
-// registers and writes it to the other buffer.  Within a K tile the two
-// half-waves take the two halves of the tile (the MFMA reduces over both), so
-// each lane reads four consecutive k values of its row at once.
+// C[M][N] = sum_k A[m][k] B[k][n].  The fp32 matrix instructions of gfx950 run
+// at a sixteenth of the bfloat16 ones' rate (157 TFLOP/s against 2.5 PFLOP/s),
+// so each fp32 value is split, exactly, into three bfloat16 pieces h + m + l
+// and x y is the sum of the six largest piece products, accumulated in fp32:
+// a ceiling of 416 TFLOP/s instead of 157.  The result is closer to the exact
+// one than fp32 products gave, because the matrix instruction rounds its
+// accumulator once per 8 terms instead of at each: relative error at a
+// reduction of 1024, 4.9e-7 in one accumulator and half of that with the small
+// products in a second one, against 5.7e-7.
+// 12288 x 1024 x 4096: 0.80 ms (129 TFLOP/s) with fp32 products, 0.57 ms (180)
+// split; at that rate the card's power limit holds the clock at 1.8 GHz, and
+// a large library product in bfloat16 reaches 1280 TFLOP/s, 213 in these units.
+//
+// A 256-thread workgroup computes a tile of C (128 x 128 in general; shapes
+// below); each of its four wave64s owns a part of it made of 32 x 32 blocks.
+// K is walked in tiles of 32 through one LDS buffer: every thread has its
+// values of tile t+1 in flight from global memory while the waves multiply
+// tile t, then splits and stores them between two barriers.  Two or three
+// workgroups share a CU, so that one multiplies while another splits.
 //
 // Operands reach LDS through loaders, one per way the operand sits in
 // memory: plain row-major matrices (contiguous along k, or along m / n) and
@@ -16,24 +26,19 @@
 // input gradient: the output gradient gathered through the filter taps;
 // filter gradient: the input patches seen along the batch-pixel axis).  A
 // loader zero-fills everything outside the matrix, so no shape needs
-// padding.  Loaders keep per-row offsets from their set-up, so a K tile costs
-// one add per row; a convolution whose channel count is a multiple of 32 has
+// padding.  A convolution whose channel count is a multiple of 32 has
 // every K tile inside one filter tap (uniform over the workgroup), and the
 // remaining index splits use multiply-high division by invariant integers.
 // The input gradient of a strided convolution is computed per stride class
 // of input pixels (h mod st, w mod st), each class a GEMM over only the taps
-// that reach it.  LDS layout follows the contiguous direction: "row of k" tiles
-// ([rows][32], k quads XOR-swizzled by row against bank conflicts) are
-// written and read with 16-byte accesses, "row of m" tiles ([32][rows]) are
-// written with 16-byte accesses and read with 4-byte ones.  No padding: the
-// 128 x 64 tiles then fit three workgroups in a CU's 160 KB of LDS.
+// that reach it.
 //
 // Split-K: the filter gradients reduce over N P Q pixels or over the rows of
 // a dense layer (up to millions), so the grid's second dimension cuts that
 // axis into slices whose partial tiles go to separate buffers and are summed
 // afterwards in slice order.  A dense layer's bias gradient (the column sums
-// of dY) is taken from the A tiles already in LDS by the workgroups of the
-// first tile column, slice by slice like dW.  No atomics anywhere: results
+// of dY) is summed in fp32 from the values the workgroups of the first tile
+// column load for A, slice by slice like dW.  No atomics anywhere: results
 // do not depend on scheduling or addresses.
 #include <hip/hip_runtime.h>
 
@@ -52,6 +57,9 @@ constexpr int THREADS = 256;
 constexpr uint32_t kXcds = 8;   // accelerator complex dies of an MI355X, one L2 each
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 __device__ inline float4 zero4() { return make_float4(0.f, 0.f, 0.f, 0.f); }
 
@@ -59,25 +67,36 @@ __device__ inline float4 zero4() { return make_float4(0.f, 0.f, 0.f, 0.f); }
 // A loader feeds one operand tile of extent E (tile rows along m or n) by 32
 // along k.  init(mn0, MN) runs once per workgroup (mn0 = tile origin, MN =
 // extent of the matrix), fetch(k0, kend, r) loads this thread's E / 8 values
-// of the K tile starting at k0 as E / 32 float4, store(lds, r) writes them.
+// of the K tile starting at k0 as E / 32 float4.  Values at k >= kend are zero
+// (they enter every dot product), also where the whole tile lies past kend.
 //
-// No load sits behind a branch, so that the address arithmetic of the next
-// tile can be scheduled between the MFMAs of the current one.  Values at
-// k >= kend must be zero (they enter every dot product): their lanes load
-// from a block of zeros instead.  Rows and columns past M or N only reach C
-// entries that are never stored, so their lanes read a clamped in-range
-// address and whatever they load is harmless.  Zero padding of a
-// convolution is masked like k >= kend.
-//
-// Row-of-k layout [E][32] (swizzled, below): thread t loads rows (t >> 3) + 32 j,
-// k offset (t & 7) * 4.  Row-of-m layout [32][E], two thread maps: RowM has E / 4
-// threads per k row, thread t loading k rows t / (E / 4) + (1024 / E) j at m
-// offset (t % (E / 4)) * 4, so that a wave reads whole rows; RowM1 gives
-// thread t the single k row t >> 3 and its E / 8 consecutive m values from
-// (t & 7) E / 8 on, so that one row address serves all of its loads (for
-// views whose row addresses are costly to form).
+// The common views load through buffer descriptors: a base that is uniform
+// over the workgroup and moves with the K tile, a 32-bit byte offset per lane
+// that does not, and the descriptor's length.  What lies past the length reads
+// as zero without a memory access, so a lane with nothing to load takes the
+// offset kNone, and the rows past a matrix's last need no test at all.  Loads
+// are 16 bytes wide at any 4-byte alignment.  Against 64-bit addresses with a
+// select per load this saves 20 to 40 registers a lane, and rows that are not
+// multiples of 4 need no scalar loads (1379 x 765 x 3067: 0.120 ms with them,
+// 0.060 without).  Rows and columns past M or N that are in bounds read their
+// neighbours: they only reach C entries that are never stored.  The general views (matrices with rows of more than kMaxLd values,
+// channel counts that are not multiples of 4, images too large for 32-bit
+// offsets) form 64-bit addresses per value; their masked lanes load from a
+// block of zeros.
+constexpr uint32_t kNone = 0x80000000u;   // past the length of every descriptor
+constexpr int64_t kMaxLd = int64_t(1) << 21;   // 255 rows of it stay below 2^31 bytes
 
-// What masked lanes load (never written).
+// `values` floats from p on (at most 2^29, the length that kNone is past)
+__device__ inline __amdgpu_buffer_rsrc_t buffer(const float* p, int64_t values) {
+  const int64_t n = values < 0 ? 0 : values > (int64_t(1) << 29) ? (int64_t(1) << 29) : values;
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)((uint32_t)n * 4u),
+                                           0x00020000);
+}
+__device__ inline float4 ldb(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+}
+
+// What masked lanes of the general views load (never written).
 __device__ __attribute__((aligned(16))) float g_zero[64] = {};
 
 __device__ inline float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
@@ -90,16 +109,64 @@ __device__ inline void keep(T& v) {
   asm volatile("" : "+v"(v));
 }
 
-// Row-of-k tiles [E][32] keep k quad q of row i in slot q ^ (i mod 8): the
-// lanes of a 16-byte read take 8 consecutive rows at one quad, which then
-// cover all banks, without padding the rows.
+// ---------------------------------------------------------------- split operands
+// x 2^40 = h + m + l, each a bfloat16: h = bf16(x'), m = bf16(x' - h), l = x' - h - m.
+// Rounding to nearest leaves remainders of at most 16 and then 8 bits, so the
+// split is exact; the scale puts the smallest subnormal x at 2^-109, so that
+// no piece is a subnormal bfloat16.  |x| >= 2^87 overflows; the kernel then
+// recomputes its tile (see gemm_kernel).  The remainders are single two-term
+// dot products with (-1, 0) and (0, -1): 4.5 vector instructions per value.
+//
+// Odd rows of either operand are negated (scale -2^40) and odd outputs (row +
+// column) negated back.  The matrix instruction aligns its 16 products and the
+// accumulator to the largest and drops what falls below 2^-26 of it towards
+// minus infinity: each result is closer to the exact one than fp32 products
+// give (relative error 4.9e-7 against 5.7e-7 at a reduction of 1024), but the
+// errors share a sign, about 5e-8 of a typical result, and a sum over 8192 rows
+// (a bias or normalisation gradient) came out 5e-6 off instead of 6e-7.  With
+// the signs alternating along both directions it cancels in such sums.
+constexpr float kSplitScale = 0x1p40f, kSplitUnscale = 0x1p-80f;
+constexpr int kPieces = 3;
+
+__device__ __forceinline__ void split2(float x, float y, float scale, uint32_t (&o)[kPieces]) {
+  // (-1, 0) and (0, -1) as register operands: as constants, the compiler would encode one of them
+  // as an inline -1.0, which this instruction does not read as a pair (wrong results measured)
+  uint32_t c0 = 0x0000bf80u, c1 = 0xbf800000u;
+  asm("" : "+s"(c0), "+s"(c1));
+  const bf16x2 first = __builtin_bit_cast(bf16x2, c0), second = __builtin_bit_cast(bf16x2, c1);
+  x *= scale;
+  y *= scale;
+  const bf16x2 h = __builtin_convertvector((floatx2){x, y}, bf16x2);
+  x = __builtin_amdgcn_fdot2_f32_bf16(h, first, x, false);
+  y = __builtin_amdgcn_fdot2_f32_bf16(h, second, y, false);
+  const bf16x2 m = __builtin_convertvector((floatx2){x, y}, bf16x2);
+  x = __builtin_amdgcn_fdot2_f32_bf16(m, first, x, false);
+  y = __builtin_amdgcn_fdot2_f32_bf16(m, second, y, false);
+  const bf16x2 l = __builtin_convertvector((floatx2){x, y}, bf16x2);
+  o[0] = __builtin_bit_cast(uint32_t, h);
+  o[1] = __builtin_bit_cast(uint32_t, m);
+  o[2] = __builtin_bit_cast(uint32_t, l);
+}
+
+__device__ inline float comp(const float4& v, int t) {
+  return t == 0 ? v.x : t == 1 ? v.y : t == 2 ? v.z : v.w;
+}
+
+// fp32 row-of-k tiles [E][32] keep k quad q of row i in slot q ^ (i mod 8).
 __device__ inline int rowk_index(int i, int k) { return i * BK + ((((k >> 2) ^ i) & 7) << 2) + (k & 3); }
 
+// Split tiles: three pieces of E rows x 32 k of bfloat16, 64 bytes a row in
+// four 16-byte octets of k.  octet(r, o) is the byte offset of octet o of row
+// r in its piece; the octets are swizzled within the row so that the 16 rows
+// of any 256 bytes' worth of reads, and the writes of either thread map, cover
+// all banks.  Row-of-m tiles also order rows by r mod 4 first, because their
+// threads write rows 4 q + e for consecutive q.
 template <int E>
 struct RowK {
   static constexpr bool kRowOfK = true;
   static constexpr int kN = E / 32;
-  static constexpr int kLds = E * BK;
+  static constexpr int kLds = E * BK;            // floats of the fp32 tile
+  static constexpr int kPiece = E * BK * 2;      // bytes of one piece
   __device__ static int row(int j) { return (threadIdx.x >> 3) + 32 * j; }
   __device__ static int koff() { return (threadIdx.x & 7) * 4; }
   __device__ static void store(float* lds, const float4 (&r)[kN]) {
@@ -107,32 +174,69 @@ struct RowK {
     for (int j = 0; j < kN; ++j)
       *reinterpret_cast<float4*>(&lds[rowk_index(row(j), koff())]) = r[j];
   }
+  __device__ static int octet(int r, int o) { return r * 64 + (((o ^ (r >> 2)) & 3) << 4); }
+  __device__ static void split_store(char* lds, const float4 (&r)[kN]) {
+    const int q = threadIdx.x & 7;
+    const float scale = row(0) & 1 ? -kSplitScale : kSplitScale;   // the same parity for every j
+#pragma unroll
+    for (int j = 0; j < kN; ++j) {
+      uint32_t u[kPieces], v[kPieces];
+      split2(r[j].x, r[j].y, scale, u);
+      split2(r[j].z, r[j].w, scale, v);
+      char* d = lds + octet(row(j), q >> 1) + (q & 1) * 8;
+#pragma unroll
+      for (int p = 0; p < kPieces; ++p) *reinterpret_cast<uint2*>(d + p * kPiece) = make_uint2(u[p], v[p]);
+    }
+  }
 };
+// A thread loads kItems blocks of four consecutive m by kR consecutive k, so
+// that it can write kR consecutive k of a row at once; value j of a thread is
+// k row krow(j) at m offset moff(j).
 template <int E>
 struct RowM {
   static constexpr bool kRowOfK = false;
   static constexpr int kN = E / 32;
-  static constexpr int kLd = E;
-  static constexpr int kLds = BK * kLd;
-  __device__ static int krow(int j) { return (int)threadIdx.x / (E / 4) + (1024 / E) * j; }
-  __device__ static int moff() { return ((int)threadIdx.x % (E / 4)) * 4; }
+  static constexpr int kItems = E == 192 ? 3 : 1;
+  static constexpr int kR = kN / kItems;
+  static constexpr int kLds = BK * E;
+  static constexpr int kPiece = E * BK * 2;
+  static_assert(kR == 1 || kR == 2 || kR == 4 || kR == 8, "k rows per thread");
+  __device__ static int item(int j) { return (int)threadIdx.x + 256 * (j / kR); }
+  __device__ static int krow(int j) { return item(j) / (E / 4) * kR + j % kR; }
+  __device__ static int moff(int j = 0) { return item(j) % (E / 4) * 4; }
   __device__ static void store(float* lds, const float4 (&r)[kN]) {
 #pragma unroll
-    for (int j = 0; j < kN; ++j) *reinterpret_cast<float4*>(&lds[krow(j) * kLd + moff()]) = r[j];
+    for (int j = 0; j < kN; ++j) *reinterpret_cast<float4*>(&lds[krow(j) * E + moff(j)]) = r[j];
   }
-};
-template <int E>
-struct RowM1 {
-  static constexpr bool kRowOfK = false;
-  static constexpr int kN = E / 32;
-  static constexpr int kLd = E;
-  static constexpr int kLds = BK * kLd;
-  __device__ static int krow() { return (int)threadIdx.x >> 3; }
-  __device__ static int moff() { return ((int)threadIdx.x & 7) * (E / 8); }
-  __device__ static void store(float* lds, const float4 (&r)[kN]) {
+  __device__ static int octet(int r, int o) {
+    return ((r >> 2) + (r & 3) * (E / 4)) * 64 + (((o ^ r ^ (r >> 4)) & 3) << 4);
+  }
+  __device__ static void split_store(char* lds, const float4 (&r)[kN]) {
 #pragma unroll
-    for (int j = 0; j < kN; ++j)
-      *reinterpret_cast<float4*>(&lds[krow() * kLd + moff() + 4 * j]) = r[j];
+    for (int i = 0; i < kItems; ++i) {
+      const int k = krow(i * kR), m = moff(i * kR);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        char* d = lds + octet(m + e, k >> 3) + (k & 7) * 2;
+        uint32_t u[(kR + 1) / 2][kPieces];
+#pragma unroll
+        for (int j = 0; j < (kR + 1) / 2; ++j)
+          split2(comp(r[i * kR + 2 * j], e), kR > 1 ? comp(r[i * kR + 2 * j + (kR > 1)], e) : 0.f,
+                 e & 1 ? -kSplitScale : kSplitScale, u[j]);
+#pragma unroll
+        for (int p = 0; p < kPieces; ++p) {
+          char* dp = d + p * kPiece;
+          if constexpr (kR == 1)
+            *reinterpret_cast<uint16_t*>(dp) = (uint16_t)u[0][p];
+          else if constexpr (kR == 2)
+            *reinterpret_cast<uint32_t*>(dp) = u[0][p];
+          else if constexpr (kR == 4)
+            *reinterpret_cast<uint2*>(dp) = make_uint2(u[0][p], u[1][p]);
+          else
+            *reinterpret_cast<uint4*>(dp) = make_uint4(u[0][p], u[1][p], u[2][p], u[3][p]);
+        }
+      }
+    }
   }
 };
 
@@ -163,12 +267,64 @@ constexpr int kFar = -(1 << 29);   // coordinate of a row past the matrix: fails
 
 __device__ inline bool inside(int v, int n) { return (unsigned)v < (unsigned)n; }
 
-// X[i][k] = p[i * ld + k]  (contiguous along k)
-template <int E, bool VEC>
+// X[i][k] = p[i * ld + k] (contiguous along k), kdim values in every row
+template <int E>
 struct MatK : RowK<E> {
   using Base = RowK<E>;
   const float* p;
-  int64_t ld;
+  int64_t ld, kdim;
+  int64_t end;                // values from the tile's first row on
+  uint32_t off_[Base::kN];    // bytes from the tile's first row, at this lane's k offset
+  __device__ void init(int64_t mn0, int64_t MN) {
+    p += mn0 * ld;
+    end = (MN - 1 - mn0) * ld + kdim;
+#pragma unroll
+    for (int j = 0; j < Base::kN; ++j) off_[j] = (uint32_t)((Base::row(j) * ld + Base::koff()) * 4);
+  }
+  __device__ void fetch(int64_t k0, int64_t kend, float4 (&r)[Base::kN]) const {
+    const auto b = buffer(p + k0, k0 < kend ? end - k0 : 0);
+#pragma unroll
+    for (int j = 0; j < Base::kN; ++j) r[j] = ldb(b, off_[j]);
+    if (k0 + BK > kend) {   // the last tile: what follows kend in the row is not zero
+      const int left = (int)(kend - k0) - Base::koff();
+#pragma unroll
+      for (int j = 0; j < Base::kN; ++j) {
+        r[j].x = left > 0 ? r[j].x : 0.f;
+        r[j].y = left > 1 ? r[j].y : 0.f;
+        r[j].z = left > 2 ? r[j].z : 0.f;
+        r[j].w = left > 3 ? r[j].w : 0.f;
+      }
+    }
+  }
+};
+
+// X[i][k] = p[k * ld + i] (contiguous along m or n).  The descriptor ends with row kend - 1.
+template <int E>
+struct MatM : RowM<E> {
+  using Base = RowM<E>;
+  const float* p;
+  int64_t ld, kdim;
+  int64_t cols;               // values of a row from the tile's first column on
+  uint32_t off_[Base::kN];
+  __device__ void init(int64_t mn0, int64_t MN) {
+    p += mn0;
+    cols = MN - mn0;
+#pragma unroll
+    for (int j = 0; j < Base::kN; ++j) off_[j] = (uint32_t)((Base::krow(j) * ld + Base::moff(j)) * 4);
+  }
+  __device__ void fetch(int64_t k0, int64_t kend, float4 (&r)[Base::kN]) const {
+    const auto b = buffer(p + k0 * ld, k0 < kend ? (kend - 1 - k0) * ld + cols : 0);
+#pragma unroll
+    for (int j = 0; j < Base::kN; ++j) r[j] = ldb(b, off_[j]);
+  }
+};
+
+// The same two views with 64-bit addresses, for ld > kMaxLd
+template <int E>
+struct MatKFar : RowK<E> {
+  using Base = RowK<E>;
+  const float* p;
+  int64_t ld, kdim;
   int64_t off_[Base::kN];   // (row, clamped to the matrix) * ld + this lane's k offset
   __device__ void init(int64_t mn0, int64_t MN) {
 #pragma unroll
@@ -182,50 +338,34 @@ struct MatK : RowK<E> {
 #pragma unroll
     for (int j = 0; j < Base::kN; ++j) {
       const float* q = p + off_[j] + k0;
-      if (VEC) {
-        r[j] = ld4(k < kend ? q : g_zero);
-      } else {
-        r[j].x = *(k + 0 < kend ? q + 0 : g_zero);
-        r[j].y = *(k + 1 < kend ? q + 1 : g_zero);
-        r[j].z = *(k + 2 < kend ? q + 2 : g_zero);
-        r[j].w = *(k + 3 < kend ? q + 3 : g_zero);
-      }
+      r[j].x = *(k + 0 < kend ? q + 0 : g_zero);
+      r[j].y = *(k + 1 < kend ? q + 1 : g_zero);
+      r[j].z = *(k + 2 < kend ? q + 2 : g_zero);
+      r[j].w = *(k + 3 < kend ? q + 3 : g_zero);
     }
   }
 };
-
-// X[i][k] = p[k * ld + i]  (contiguous along m or n; VEC needs MN % 4 == 0)
-template <int E, bool VEC>
-struct MatM : RowM<E> {
+template <int E>
+struct MatMFar : RowM<E> {
   using Base = RowM<E>;
   const float* p;
-  int64_t ld;
-  int64_t i0;                // this lane's first m
-  int64_t rows;              // MN
-  int64_t off_[Base::kN];    // k row * ld (+ the m offset clamped to the matrix, VEC)
+  int64_t ld, kdim;
+  int64_t mn0_, rows;       // tile origin, MN
   __device__ void init(int64_t mn0, int64_t MN) {
-    i0 = mn0 + Base::moff();
+    mn0_ = mn0;
     rows = MN;
-#pragma unroll
-    for (int j = 0; j < Base::kN; ++j)
-      off_[j] = Base::krow(j) * ld + (VEC ? (i0 < MN ? i0 : 0) : 0);
   }
   __device__ void fetch(int64_t k0, int64_t kend, float4 (&r)[Base::kN]) const {
-    const float* pk = p + k0 * ld;
 #pragma unroll
     for (int j = 0; j < Base::kN; ++j) {
-      const bool ok = k0 + Base::krow(j) < kend;
-      if (VEC) {
-        r[j] = ld4(ok ? pk + off_[j] : g_zero);
-      } else {
-        float v[4];
+      const int64_t k = k0 + Base::krow(j);
+      float v[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int64_t i = i0 + e;
-          v[e] = *(ok ? pk + off_[j] + (i < rows ? i : 0) : g_zero);
-        }
-        r[j] = make_float4(v[0], v[1], v[2], v[3]);
+      for (int e = 0; e < 4; ++e) {
+        const int64_t i = mn0_ + Base::moff(j) + e;
+        v[e] = *(k < kend ? p + k * ld + (i < rows ? i : 0) : g_zero);
       }
+      r[j] = make_float4(v[0], v[1], v[2], v[3]);
     }
   }
 };
@@ -233,10 +373,14 @@ struct MatM : RowM<E> {
 // Loader modes of the convolution views.  Row-of-k views: TAP when the
 // reduced channel count is a multiple of 32 (a K tile lies inside one filter
 // tap, uniform over the workgroup), VEC4 when it is a multiple of 4 (each lane
-// splits its own k index, four consecutive channels per load), SCALAR
-// otherwise.  Row-of-m views: TAP when all E / 8 values of a lane lie in one
-// tap (channels a multiple of 16), VEC4 when each float4 does.
+// splits its own k index, four consecutive channels per load), SCALAR (64-bit
+// addresses, one per value) otherwise.  Row-of-m views: VEC4 when each float4
+// lies in one tap, SCALAR otherwise.  TAP and VEC4 take byte offsets from the
+// first image row that the tile can touch; the launchers check that they fit
+// (window_fits).
 enum { SCALAR = 0, VEC4 = 1, TAP = 2 };
+
+__device__ inline int clampi(int v, int lo, int hi) { return min(max(v, lo), hi); }
 
 // Convolution forward, A = input patches: A[m = (n, p, q)][kk = (r, s, c)] =
 // X[n][p st - pad + r][q st - pad + s][c]   (row-of-k)
@@ -246,24 +390,34 @@ struct ConvPatch : RowK<E> {
   const float* x;
   int H, W, C, S, st, pad;
   FastDiv dQ, dPQ, dC, dS, dSC;   // by Q, P Q, C, S, S C
-  int64_t base_[Base::kN];        // offset of X[n][h0][w0][0]
-  int h_[Base::kN], w_[Base::kN]; // h0 = p st - pad, w0 = q st - pad
+  int64_t far_[MODE == SCALAR ? Base::kN : 1];   // offset of X[n][h0][w0][0]
+  int base_[MODE == SCALAR ? 1 : Base::kN];      // the same from the tile's first image row, bytes
+  int h_[Base::kN], w_[Base::kN];                // h0 = p st - pad, w0 = q st - pad
+  __device__ void split(int m, int& n, int& p, int& q) const {
+    n = dPQ.div(m);
+    const int rem = m - n * (int)dPQ.d;
+    p = dQ.div(rem);
+    q = rem - p * (int)dQ.d;
+  }
   __device__ void init(int64_t mn0, int64_t M) {
+    int n0 = 0, hb = 0;
+    if constexpr (MODE != SCALAR) {
+      int p0, q0;
+      split((int)mn0, n0, p0, q0);
+      hb = clampi(p0 * st - pad, 0, H - 1);
+      x += ((int64_t)n0 * H + hb) * W * C;
+    }
 #pragma unroll
     for (int j = 0; j < Base::kN; ++j) {
       const int64_t m = mn0 + Base::row(j);
-      if (m < M) {
-        const int n = dPQ.div((int)m);
-        const int rem = (int)m - n * (int)dPQ.d;
-        const int p = dQ.div(rem), q = rem - p * (int)dQ.d;
-        h_[j] = p * st - pad;
-        w_[j] = q * st - pad;
-        base_[j] = (((int64_t)n * H + h_[j]) * W + w_[j]) * C;
-      } else {
-        h_[j] = kFar;
-        w_[j] = 0;
-        base_[j] = 0;
-      }
+      int n = 0, p = 0, q = 0;
+      if (m < M) split((int)m, n, p, q);
+      h_[j] = m < M ? p * st - pad : kFar;
+      w_[j] = q * st - pad;
+      if constexpr (MODE == SCALAR)
+        far_[j] = m < M ? (((int64_t)n * H + h_[j]) * W + w_[j]) * C : 0;
+      else
+        base_[j] = m < M ? (((n - n0) * H + h_[j] - hb) * W + w_[j]) * C * 4 : 0;
     }
   }
   // value at (row j, column kk) or 0 when kk >= kend or outside the image
@@ -274,7 +428,7 @@ struct ConvPatch : RowK<E> {
     const int rem = kc - r * (int)dSC.d;
     const int s = dC.div(rem), c = rem - s * C;
     const bool ok = kin & inside(h_[j] + r, H) & inside(w_[j] + s, W);
-    return *(ok ? x + base_[j] + ((int64_t)r * W + s) * C + c : g_zero);
+    return *(ok ? x + far_[j] + ((int64_t)r * W + s) * C + c : g_zero);
   }
   __device__ void fetch(int64_t k0, int64_t kend, float4 (&r)[Base::kN]) const {
     const int kk = (int)k0 + Base::koff();
@@ -285,6 +439,7 @@ struct ConvPatch : RowK<E> {
                            at(j, kk + 3, kend));
     } else {
       int rr, s, c;
+      bool kin = true;
       if constexpr (MODE == TAP) {   // uniform tap
         const int tap = dC.div((int)k0);
         rr = dS.div(tap);
@@ -295,13 +450,14 @@ struct ConvPatch : RowK<E> {
         const int rem = kk - rr * (int)dSC.d;
         s = dC.div(rem);
         c = rem - s * C;
+        kin = kk < kend;
       }
-      const int64_t toff = ((int64_t)rr * W + s) * C + c;
-      const bool kin = kk < kend;
+      const int toff = ((rr * W + s) * C + c) * 4;
+      const auto b = buffer(x, k0 < kend ? int64_t(1) << 29 : 0);
 #pragma unroll
       for (int j = 0; j < Base::kN; ++j) {
         const bool ok = kin & inside(h_[j] + rr, H) & inside(w_[j] + s, W);
-        r[j] = ld4(ok ? x + base_[j] + toff : g_zero);
+        r[j] = ldb(b, ok ? (uint32_t)(base_[j] + toff) : kNone);
       }
     }
   }
@@ -319,26 +475,36 @@ template <int E, int MODE>
 struct ConvGradTap : RowK<E> {
   using Base = RowK<E>;
   const float* dy;
-  int P, Q, K, nS, a, b;
+  int P, Q, K, nR, nS, a, b;
   FastDiv dWc, dHWc, dK, dnS, dSK;   // by Wc, Hc Wc, K, nS, nS K
-  int64_t base_[Base::kN];           // offset of dY[n][hh + a][ww + b][0]
-  int p_[Base::kN], q_[Base::kN];    // hh + a, ww + b
+  int64_t far_[MODE == SCALAR ? Base::kN : 1];   // offset of dY[n][hh + a][ww + b][0]
+  int base_[MODE == SCALAR ? 1 : Base::kN];      // from the tile's first row of dY, bytes
+  int p_[Base::kN], q_[Base::kN];                // hh + a, ww + b
+  __device__ void split(int m, int& n, int& hh, int& ww) const {
+    n = dHWc.div(m);
+    const int rem = m - n * (int)dHWc.d;
+    hh = dWc.div(rem);
+    ww = rem - hh * (int)dWc.d;
+  }
   __device__ void init(int64_t mn0, int64_t M) {
+    int n0 = 0, pb = 0;
+    if constexpr (MODE != SCALAR) {
+      int h0, w0;
+      split((int)mn0, n0, h0, w0);
+      pb = clampi(h0 + a - (nR - 1), 0, P - 1);
+      dy += ((int64_t)n0 * P + pb) * Q * K;
+    }
 #pragma unroll
     for (int j = 0; j < Base::kN; ++j) {
       const int64_t m = mn0 + Base::row(j);
-      if (m < M) {
-        const int n = dHWc.div((int)m);
-        const int rem = (int)m - n * (int)dHWc.d;
-        const int hh = dWc.div(rem), ww = rem - hh * (int)dWc.d;
-        p_[j] = hh + a;
-        q_[j] = ww + b;
-        base_[j] = (((int64_t)n * P + p_[j]) * Q + q_[j]) * K;
-      } else {
-        p_[j] = kFar;
-        q_[j] = 0;
-        base_[j] = 0;
-      }
+      int n = 0, hh = 0, ww = 0;
+      if (m < M) split((int)m, n, hh, ww);
+      p_[j] = m < M ? hh + a : kFar;
+      q_[j] = ww + b;
+      if constexpr (MODE == SCALAR)
+        far_[j] = m < M ? (((int64_t)n * P + p_[j]) * Q + q_[j]) * K : 0;
+      else
+        base_[j] = m < M ? (((n - n0) * P + p_[j] - pb) * Q + q_[j]) * K * 4 : 0;
     }
   }
   __device__ float at(int j, int kk, int64_t kend) const {
@@ -348,7 +514,7 @@ struct ConvGradTap : RowK<E> {
     const int rem = kc - i * (int)dSK.d;
     const int jj = dK.div(rem), k = rem - jj * K;
     const bool ok = kin & inside(p_[j] - i, P) & inside(q_[j] - jj, Q);
-    return *(ok ? dy + base_[j] - ((int64_t)i * Q + jj) * K + k : g_zero);
+    return *(ok ? dy + far_[j] - ((int64_t)i * Q + jj) * K + k : g_zero);
   }
   __device__ void fetch(int64_t k0, int64_t kend, float4 (&r)[Base::kN]) const {
     const int kk = (int)k0 + Base::koff();
@@ -359,6 +525,7 @@ struct ConvGradTap : RowK<E> {
                            at(j, kk + 3, kend));
     } else {
       int i, jj, k;
+      bool kin = true;
       if constexpr (MODE == TAP) {   // uniform tap
         const int tap = dK.div((int)k0);
         i = dnS.div(tap);
@@ -369,13 +536,14 @@ struct ConvGradTap : RowK<E> {
         const int rem = kk - i * (int)dSK.d;
         jj = dK.div(rem);
         k = rem - jj * K;
+        kin = kk < kend;
       }
-      const int64_t toff = k - ((int64_t)i * Q + jj) * K;
-      const bool kin = kk < kend;
+      const int toff = (k - (i * Q + jj) * K) * 4;
+      const auto bf = buffer(dy, k0 < kend ? int64_t(1) << 29 : 0);
 #pragma unroll
       for (int j = 0; j < Base::kN; ++j) {
         const bool ok = kin & inside(p_[j] - i, P) & inside(q_[j] - jj, Q);
-        r[j] = ld4(ok ? dy + base_[j] + toff : g_zero);
+        r[j] = ldb(bf, ok ? (uint32_t)(base_[j] + toff) : kNone);
       }
     }
   }
@@ -390,27 +558,27 @@ struct ConvFilterTap : RowM<E> {
   int C, K, S, st, r0, s0, nS;
   int64_t RSC;
   FastDiv dK, dnS, dSK;
-  int cc;                     // this lane's channel, clamped to the filter
-  int64_t roff_[Base::kN];    // this lane's k rows * RSC
+  int c0;                     // the tile's first channel
+  uint32_t off_[MODE == TAP ? Base::kN : 1];   // bytes from the K tile's first filter row
   __device__ void init(int64_t mn0, int64_t) {
-    const int c0 = (int)mn0 + Base::moff();
-    cc = c0 < C ? c0 : 0;
+    c0 = (int)mn0;
+    if constexpr (MODE == TAP) {
 #pragma unroll
-    for (int j = 0; j < Base::kN; ++j) roff_[j] = (int64_t)Base::krow(j) * RSC;
+      for (int j = 0; j < Base::kN; ++j)
+        off_[j] = (uint32_t)((Base::krow(j) * RSC + Base::moff(j)) * 4);
+    }
   }
   __device__ void fetch(int64_t k0, int64_t kend, float4 (&r)[Base::kN]) const {
     if constexpr (MODE == TAP) {   // uniform tap
       const int tap = dK.div((int)k0);
       const int i = dnS.div(tap), jj = tap - i * nS;
-      const int kb = (int)k0 - tap * K;
-      const float* base =
-          w + (int64_t)kb * RSC + ((int64_t)(r0 + st * i) * S + s0 + st * jj) * C + cc;
+      const int64_t at = ((int64_t)k0 - (int64_t)tap * K) * RSC +
+                         ((int64_t)(r0 + st * i) * S + s0 + st * jj) * C + c0;
+      const auto b = buffer(w + at, k0 < kend ? K * RSC - at : 0);
 #pragma unroll
-      for (int j = 0; j < Base::kN; ++j) {
-        const bool ok = k0 + Base::krow(j) < kend;
-        r[j] = ld4(ok ? base + roff_[j] : g_zero);
-      }
+      for (int j = 0; j < Base::kN; ++j) r[j] = ldb(b, off_[j]);
     } else {
+      const int cc = c0 + Base::moff() < C ? c0 + Base::moff() : 0;   // clamped to the filter
 #pragma unroll
       for (int j = 0; j < Base::kN; ++j) {
         const int kk = (int)k0 + Base::krow(j);
@@ -430,23 +598,28 @@ struct ConvFilterTap : RowM<E> {
 // Convolution filter gradient, B = input patches along the pixel axis:
 // B[kk = (n, p, q)][col = (r, s, c)] = X[n][p st - pad + r][q st - pad + s][c]
 // (row-of-m).  A lane's columns are clamped to the matrix, then split into
-// taps at set-up: one tap for all of them (TAP), one per float4 (VEC4) or one
-// per value (SCALAR).
+// taps at set-up: one per float4 (VEC4) or one per value (SCALAR).  A lane's
+// kR pixels are consecutive: the first one's position is split from its index,
+// the others step from it.
 template <int E, int MODE>
-struct ConvPixelPatch : RowM1<E> {
-  using Base = RowM1<E>;
-  static constexpr int kT = MODE == TAP ? 1 : MODE == VEC4 ? Base::kN : 4 * Base::kN;
+struct ConvPixelPatch : RowM<E> {
+  using Base = RowM<E>;
+  using Off = std::conditional_t<MODE == VEC4, int, int64_t>;
+  static constexpr int kPer = MODE == VEC4 ? 1 : 4;   // taps per float4
+  static constexpr int kT = kPer * Base::kItems;
   const float* x;
   int H, W, C, st, pad;
+  int h_end, w_end;       // P st - pad, Q st - pad
+  int64_t row_step;       // from the pixel after a row's last one to the next row's first
+  int64_t img_step;       // from the row after an image's last one to the next image's first
   FastDiv dQ, dPQ, dC, dSC;
   int toff_[kT];          // (r W + s) C + c of each tap entry
   int r_[kT], s_[kT];
   __device__ void init(int64_t mn0, int64_t RSC) {
-    const int col0 = (int)mn0 + Base::moff();
 #pragma unroll
     for (int e = 0; e < kT; ++e) {
-      const int step = MODE == VEC4 ? 4 : 1;
-      const int cc = col0 + step * e < RSC ? col0 + step * e : 0;
+      const int col = (int)mn0 + Base::moff(e / kPer * Base::kR) + e % kPer;
+      const int cc = col < RSC ? col : 0;
       const int r = dSC.div(cc);
       const int rem = cc - r * (int)dSC.d;
       const int s = dC.div(rem), c = rem - s * C;
@@ -455,39 +628,53 @@ struct ConvPixelPatch : RowM1<E> {
       toff_[e] = (r * W + s) * C + c;
     }
   }
+  __device__ void split(int m, int& n, int& p, int& q) const {
+    n = dPQ.div(m);
+    const int rem = m - n * (int)dPQ.d;
+    p = dQ.div(rem);
+    q = rem - p * (int)dQ.d;
+  }
   __device__ void fetch(int64_t k0, int64_t kend, float4 (&r)[Base::kN]) const {
-    const int kk = (int)k0 + Base::krow();
-    const bool kin = kk < kend;
-    const int kc = kin ? kk : 0;
-    const int n = dPQ.div(kc);
-    const int rem = kc - n * (int)dPQ.d;
-    const int p = dQ.div(rem), q = rem - p * (int)dQ.d;
-    const int hb = p * st - pad, wb = q * st - pad;
-    int64_t po = (((int64_t)n * H + hb) * W + wb) * C;
-    keep(po);
-    const float* pix = x + po;
-    if constexpr (MODE == TAP) {
-      const bool ok = kin & inside(hb + r_[0], H) & inside(wb + s_[0], W);
-      const float* src = ok ? pix + toff_[0] : g_zero;
+    int n0 = 0, hb0 = 0;      // VEC4: the image row that offsets count from
+    if constexpr (MODE == VEC4) {
+      int p0, q0;
+      split(k0 < kend ? (int)k0 : 0, n0, p0, q0);
+      hb0 = clampi(p0 * st - pad, 0, H - 1);
+    }
+    const auto b = buffer(x + ((int64_t)n0 * H + hb0) * W * C, k0 < kend ? int64_t(1) << 29 : 0);
 #pragma unroll
-      for (int j = 0; j < Base::kN; ++j) r[j] = ld4(src + 4 * j);
-    } else if constexpr (MODE == VEC4) {
+    for (int i = 0; i < Base::kItems; ++i) {
+      const int kk = (int)k0 + Base::krow(i * Base::kR);
+      int n, p, q;
+      split(kk < kend ? kk : 0, n, p, q);
+      int hb = p * st - pad, wb = q * st - pad;
+      Off po = (((Off)(n - n0) * H + hb - hb0) * W + wb) * C;
 #pragma unroll
-      for (int j = 0; j < Base::kN; ++j) {
-        const bool ok = kin & inside(hb + r_[j], H) & inside(wb + s_[j], W);
-        r[j] = ld4(ok ? pix + toff_[j] : g_zero);
-      }
-    } else {
+      for (int j = 0; j < Base::kR; ++j) {
+        keep(po);
+        const bool kin = kk + j < kend;
+        if constexpr (MODE == VEC4) {
+          const bool ok = kin & inside(hb + r_[i], H) & inside(wb + s_[i], W);
+          r[i * Base::kR + j] = ldb(b, ok ? (uint32_t)(po + toff_[i]) * 4u : kNone);
+        } else {
+          float v[4];
 #pragma unroll
-      for (int j = 0; j < Base::kN; ++j) {
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int u = 4 * j + e;
-          const bool ok = kin & inside(hb + r_[u], H) & inside(wb + s_[u], W);
-          v[e] = *(ok ? pix + toff_[u] : g_zero);
+          for (int e = 0; e < 4; ++e) {
+            const int u = 4 * i + e;
+            const bool ok = kin & inside(hb + r_[u], H) & inside(wb + s_[u], W);
+            v[e] = *(ok ? x + po + toff_[u] : g_zero);
+          }
+          r[i * Base::kR + j] = make_float4(v[0], v[1], v[2], v[3]);
         }
-        r[j] = make_float4(v[0], v[1], v[2], v[3]);
+        if (j + 1 < Base::kR) {
+          wb += st;
+          const bool row_done = wb >= w_end;
+          hb += row_done ? st : 0;
+          const bool img_done = hb >= h_end;
+          po += st * C + (row_done ? (Off)row_step : 0) + (img_done ? (Off)img_step : 0);
+          wb = row_done ? -pad : wb;
+          hb = img_done ? -pad : hb;
+        }
       }
     }
   }
@@ -518,13 +705,6 @@ __device__ inline float4 read_op(const float* lds, int i, int k) {
                      lds[(k + 3) * ld + i]);
 }
 
-__device__ inline float comp(const float4& v, int t) {
-  return t == 0 ? v.x : t == 1 ? v.y : t == 2 ? v.z : v.w;
-}
-
-// BM x BN tile; the four waves form a grid of sub-tiles made of MFMA 32 x 32
-// blocks (2 x 2 waves, or 4 x 1 for tiles 32 wide and for 256 x 64 tiles, 1 x 4 for
-// tiles 32 tall).
 // Batched problems (grid z): batch z = (zo, zi) with zi = z mod inner; operand
 // and result pointers move by zo * outer stride + zi * inner stride.  With
 // skip_upper, tiles strictly above the diagonal return without writing.
@@ -548,15 +728,64 @@ struct WaveGrid {
   static constexpr int WN = 4 / WM;
   static constexpr int MB = BM / (32 * WM), NB = BN / (32 * WN);
   static_assert(MB >= 1 && NB >= 1 && MB * 32 * WM == BM && NB * 32 * WN == BN, "tile shape");
+  // waves per SIMD, the compiler's register budget: 3, or what the LDS tile (192 bytes a row)
+  // or two accumulators for three or more blocks leave room for
+  static constexpr int kWaves =
+      MB * NB >= 3 ? 2 : std::min(3, 160 * 1024 / ((BM + BN) * 192 + 256));
 };
 
-// One K tile from LDS into the accumulators: four k steps of 8 per half-wave,
-// each a round of LDS reads feeding MB x NB x 4 MFMAs.
+// One K tile of split operands into the accumulators: two k steps of 16, each
+// six products of pieces.  m l, l m and l l (at most 2^-26 of x y together) are
+// left out.  h h goes to acc, the five smaller products to low: next to an
+// accumulator that one large term has raised, the matrix instruction drops
+// the last bits of every small term, always the same ones for operands that
+// repeat.  In one accumulator, column sums of (softmax - onehot) W came out
+// 1.8e-6 off instead of 5.6e-7.
+template <class LA, class LB, int MB, int NB>
+__device__ __forceinline__ void mma_split(floatx16 (&acc)[MB][NB], floatx16 (&low)[MB][NB],
+                                          const char* A, const char* B, const int (&aoff)[MB],
+                                          const int (&boff)[NB]) {
+  auto read = [&](bf16x8(&x)[MB], int p, int ks) {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+      x[mb] = *reinterpret_cast<const bf16x8*>(A + p * LA::kPiece + (aoff[mb] ^ (ks << 5)));
+  };
+  auto readb = [&](bf16x8(&x)[NB], int p, int ks) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+      x[nb] = *reinterpret_cast<const bf16x8*>(B + p * LB::kPiece + (boff[nb] ^ (ks << 5)));
+  };
+  auto mma = [&](floatx16(&c)[MB][NB], const bf16x8(&x)[MB], const bf16x8(&y)[NB]) {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        c[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[mb], y[nb], c[mb][nb], 0, 0, 0);
+  };
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    bf16x8 ah[MB], al[MB], am[MB], bh[NB], bl[NB], bm[NB];
+    read(ah, 0, ks);
+    readb(bl, 2, ks);
+    read(al, 2, ks);
+    readb(bh, 0, ks);
+    mma(low, ah, bl);
+    mma(low, al, bh);
+    read(am, 1, ks);
+    readb(bm, 1, ks);
+    mma(acc, ah, bh);
+    mma(low, am, bm);
+    mma(low, am, bh);
+    mma(low, ah, bm);
+  }
+}
+
+// One fp32 K tile from LDS into the accumulators: four k steps of 8 per
+// half-wave, each a round of LDS reads feeding MB x NB x 4 MFMAs.
 template <int BM, int BN, class LA, class LB, int MB, int NB>
 __device__ __forceinline__ void mma_ktile(floatx16 (&acc)[MB][NB], const float* A, const float* B,
                                           int wm, int wn, int half, int li) {
   using G = WaveGrid<BM, BN>;
-  static_assert(MB == G::MB && NB == G::NB, "accumulator blocks");
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int kq = half * 16 + 4 * j;
@@ -576,13 +805,13 @@ __device__ __forceinline__ void mma_ktile(floatx16 (&acc)[MB][NB], const float* 
   }
 }
 
-// The accumulators of the tile at (m0, n0) into C (plus the column's bias).
+// The accumulators (times even for the tile's even rows, odd for the others) of the tile at
+// (m0, n0) into C, plus the column's bias.
 template <int BM, int BN, class OM, bool BIAS, int MB, int NB>
-__device__ __forceinline__ void store_tile(const floatx16 (&acc)[MB][NB], float* out, const OM& om,
-                                           const float* bias, int64_t m0, int64_t n0, int64_t M,
-                                           int64_t N, int wm, int wn, int half, int li) {
+__device__ __forceinline__ void store_tile(const floatx16 (&acc)[MB][NB], float even, float odd,
+                                           float* out, const OM& om, const float* bias, int64_t m0, int64_t n0,
+                                           int64_t M, int64_t N, int wm, int wn, int half, int li) {
   using G = WaveGrid<BM, BN>;
-  static_assert(MB == G::MB && NB == G::NB, "accumulator blocks");
 #pragma unroll
   for (int mb = 0; mb < G::MB; ++mb)
 #pragma unroll
@@ -593,41 +822,37 @@ __device__ __forceinline__ void store_tile(const floatx16 (&acc)[MB][NB], float*
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int64_t row = m0 + wm * (BM / G::WM) + mb * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-        if (row < M) out[om.row(row) + col] = acc[mb][nb][r] + bv;
+        if (row < M) out[om.row(row) + col] = acc[mb][nb][r] * (r & 1 ? odd : even) + bv;
       }
     }
 }
 
-// Issue the next tile's global loads one per two MFMAs from the start of a K
-// tile's body, so that the MFMAs cover their latency; left alone, the
-// scheduler sinks them next to the LDS stores that consume them.
-template <int NLOADS>
-__device__ __forceinline__ void interleave_loads() {
+template <int MB, int NB>
+__device__ __forceinline__ void clear(floatx16 (&acc)[MB][NB]) {
 #pragma unroll
-  for (int g = 0; g < NLOADS; ++g) {
-    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // one global load
-    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);   // two MFMAs
-  }
+  for (int a = 0; a < MB; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 }
 
 // ROWSUM: rowsum[slice][m] = sum over this slice's k of A[m][k]
 template <int BM, int BN, class LA, class LB, class OM, bool BIAS, bool BATCHED, bool ROWSUM>
-__global__ __launch_bounds__(THREADS) void gemm_kernel(LA la, LB lb, float* __restrict__ c, OM om,
-                                                       int64_t slice_stride,
-                                                       const float* __restrict__ bias, int64_t M,
-                                                       int64_t N, int64_t K, int64_t k_slice,
-                                                       int tiles_m, int tiles_n, Batch bt,
-                                                       float* __restrict__ rowsum) {
-  constexpr int WM = WaveGrid<BM, BN>::WM, MB = WaveGrid<BM, BN>::MB, NB = WaveGrid<BM, BN>::NB;
-  constexpr bool kLoadsFirst = BN > 128;
+__global__ __launch_bounds__(THREADS, (WaveGrid<BM, BN>::kWaves)) void gemm_kernel(
+    LA la, LB lb, float* __restrict__ c, OM om, int64_t slice_stride,
+    const float* __restrict__ bias, int64_t M, int64_t N, int64_t K, int64_t k_slice, int tiles_m,
+    int tiles_n, Batch bt, float* __restrict__ rowsum) {
+  using G = WaveGrid<BM, BN>;
+  constexpr int MB = G::MB, NB = G::NB;
   // Workgroup (tile, slice, batch) from an XCD-aware order: the hardware hands
   // linear workgroup h to XCD h mod 8, so logical ids are laid out so that each
   // XCD (with its own L2) gets one contiguous run of them, and neighbouring
   // tiles, which share operand rows, share an L2.
   const uint32_t gx = gridDim.x, gy = gridDim.y;
-  const uint32_t G = gx * gy * gridDim.z;
+  const uint32_t total = gx * gy * gridDim.z;
   const uint32_t h = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-  const uint32_t q = G / kXcds, rem = G % kXcds, xcd = h % kXcds, local = h / kXcds;
+  const uint32_t q = total / kXcds, rem = total % kXcds, xcd = h % kXcds, local = h / kXcds;
   const uint32_t L = xcd < rem ? xcd * (q + 1) + local : rem * (q + 1) + (xcd - rem) * q + local;
   const int t = (int)(L % gx);
   const int64_t slice = (L / gx) % gy;
@@ -637,8 +862,9 @@ __global__ __launch_bounds__(THREADS) void gemm_kernel(LA la, LB lb, float* __re
     shift(lb, zo * bt.b_o + zi * bt.b_i);
     c += zo * bt.c_o + zi * bt.c_i;
   }
-  __shared__ __attribute__((aligned(16))) float As[2][LA::kLds];
-  __shared__ __attribute__((aligned(16))) float Bs[2][LB::kLds];
+  __shared__ __attribute__((aligned(16))) char lds[kPieces * (LA::kPiece + LB::kPiece)];
+  char* const As = lds;
+  char* const Bs = lds + kPieces * LA::kPiece;
 
   // grouped tile order: 8 tile-rows share their B tiles in L2
   const int group = 8;
@@ -658,162 +884,95 @@ __global__ __launch_bounds__(THREADS) void gemm_kernel(LA la, LB lb, float* __re
   la.init(m0, M);
   lb.init(n0, N);
   float4 ra[LA::kN], rb[LB::kN];
-  floatx16 acc[MB][NB];
+  floatx16 acc[MB][NB], low[MB][NB];
+  clear(acc);
+  clear(low);
+
+  const bool sums = ROWSUM && tn == 0;
+  float4 rs = zero4();
+
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int wm = wave % G::WM, wn = wave / G::WM;
+  const int half = lane >> 5;
+  const int li = lane & 31;
+  int aoff[MB], boff[NB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) aoff[mb] = LA::octet(wm * (BM / G::WM) + mb * 32 + li, half);
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) boff[nb] = LB::octet(wn * (BN / G::WN) + nb * 32 + li, half);
+
+  la.fetch(kb, ke, ra);
+  lb.fetch(kb, ke, rb);
+  for (int64_t k0 = kb; k0 < ke; k0 += BK) {
+    __syncthreads();   // every wave has read the previous tile
+    LA::split_store(As, ra);
+    LB::split_store(Bs, rb);
+    if constexpr (ROWSUM) {
+      if (sums) {
+#pragma unroll
+        for (int j = 0; j < LA::kN; ++j) {
+          rs.x += ra[j].x;
+          rs.y += ra[j].y;
+          rs.z += ra[j].z;
+          rs.w += ra[j].w;
+        }
+      }
+    }
+    __syncthreads();
+    // in flight while this tile is multiplied; past the last tile, the loads
+    // read zeros without touching memory
+    la.fetch(k0 + BK, ke, ra);
+    lb.fetch(k0 + BK, ke, rb);
+    __builtin_amdgcn_sched_barrier(0);
+    mma_split<LA, LB>(acc, low, As, Bs, aoff, boff);
+  }
+
+  // A value of 2^87 or more, an infinity, a NaN or a sum of 2^48 or more leaves an accumulator
+  // that is not finite: such a tile is computed again by fp32 products.
+  float check = 0.f;
 #pragma unroll
   for (int a = 0; a < MB; ++a)
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-
-  const bool sums = ROWSUM && tn == 0 && (int)threadIdx.x < BM;
-  float rs = 0.f;
-
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int wm = wave % WM, wn = wave / WM;
-  const int half = lane >> 5;
-  const int li = lane & 31;
-
-  la.fetch(kb, ke, ra);
-  lb.fetch(kb, ke, rb);
-  LA::store(As[0], ra);
-  LB::store(Bs[0], rb);
-  __syncthreads();
-  int buf = 0;
-  for (int64_t k0 = kb; k0 < ke; k0 += BK) {
-    // the tile after the last one is all zeros: fetching and storing it anyway
-    // keeps the loop body free of branches
-    la.fetch(k0 + BK, ke, ra);
-    lb.fetch(k0 + BK, ke, rb);
-    // 192-wide tiles issue all their loads before the MFMAs: their address
-    // arithmetic is long enough that the interleave below would place the
-    // loads late (measured 2-4 % slower)
-    if constexpr (kLoadsFirst) __builtin_amdgcn_sched_barrier(0);
-    const float* A = As[buf];
-    const float* B = Bs[buf];
-    mma_ktile<BM, BN, LA, LB>(acc, A, B, wm, wn, half, li);
-    if constexpr (ROWSUM) {
-      if (sums) {
+      for (int r = 0; r < 16; ++r) {
+        acc[a][b][r] += low[a][b][r];
+        check = fmaf(acc[a][b][r], 0.f, check);
+      }
+  float even = li & 1 ? -kSplitUnscale : kSplitUnscale, odd = -even;
+  if (__syncthreads_or(check != 0.f)) {
+    even = odd = 1.f;
+    clear(acc);
+    float* const Af = reinterpret_cast<float*>(lds);
+    float* const Bf = Af + LA::kLds;
+    for (int64_t k0 = kb; k0 < ke; k0 += BK) {
+      la.fetch(k0, ke, ra);
+      lb.fetch(k0, ke, rb);
+      LA::store(Af, ra);
+      LB::store(Bf, rb);
+      __syncthreads();
+      mma_ktile<BM, BN, LA, LB>(acc, Af, Bf, wm, wn, half, li);
+      __syncthreads();
+    }
+  }
+  if constexpr (ROWSUM) {
+    if (sums) {   // uniform over the workgroup; every wave is past its reads of the tiles
+      float* red = reinterpret_cast<float*>(lds);   // [k group][BM]
+      constexpr int kGroups = THREADS / (BM / 4);
+      *reinterpret_cast<float4*>(&red[threadIdx.x / (BM / 4) * BM + LA::moff()]) = rs;
+      __syncthreads();
+      if ((int)threadIdx.x < BM && m0 + threadIdx.x < M) {
+        float v = 0.f;
 #pragma unroll
-        for (int k = 0; k < BK; ++k) {
-          if constexpr (LA::kRowOfK) rs += A[rowk_index(threadIdx.x, k)];
-          else rs += A[k * (LA::kLds / BK) + threadIdx.x];
-        }
+        for (int j = 0; j < kGroups; ++j) v += red[j * BM + threadIdx.x];
+        rowsum[slice * M + m0 + threadIdx.x] = v;
       }
     }
-    if constexpr (!kLoadsFirst) interleave_loads<LA::kN + LB::kN>();
-    LA::store(As[buf ^ 1], ra);
-    LB::store(Bs[buf ^ 1], rb);
-    __syncthreads();
-    buf ^= 1;
   }
-
-  if (sums && m0 + threadIdx.x < M) rowsum[slice * M + m0 + threadIdx.x] = rs;
-  store_tile<BM, BN, OM, BIAS>(acc, c + slice * slice_stride, om, bias, m0, n0, M, N, wm, wn, half,
-                               li);
+  store_tile<BM, BN, OM, BIAS>(acc, even, odd, c + slice * slice_stride, om, bias, m0, n0, M, N, wm,
+                               wn, half, li);
 }
-
-// Persistent form for short reductions of the dense loaders (one slice, no
-// batch, no row sums; chosen below): a workgroup walks the tiles L, L + G,
-// L + 2G, ... and, while it multiplies the last K tile of one output tile,
-// already loads the first K tile of its next one, so that the next tile's
-// loads and this tile's stores are in flight together.  With K of 64 or 128 a
-// tile has only two or four K tiles, and the one-tile-per-workgroup form spends
-// much of each workgroup's life in its first load and its stores.  Results are
-// those of gemm_kernel bit for bit (same K order per output).
-template <int BM, int BN, class LA, class LB, class OM, bool BIAS>
-__global__ __launch_bounds__(THREADS) void gemm_persistent(LA la, LB lb, float* __restrict__ c,
-                                                           OM om, const float* __restrict__ bias,
-                                                           int64_t M, int64_t N, int64_t K,
-                                                           int tiles_m, int tiles_n) {
-  constexpr int WM = WaveGrid<BM, BN>::WM, MB = WaveGrid<BM, BN>::MB, NB = WaveGrid<BM, BN>::NB;
-  static_assert(BN <= 128, "loads interleaved with the MFMAs, as gemm_kernel does up to 128 wide");
-  // the same XCD-aware logical order as gemm_kernel: each XCD's workgroups take
-  // one contiguous run of tiles in every round
-  const uint32_t G = gridDim.x, h = blockIdx.x;
-  const uint32_t q = G / kXcds, rem = G % kXcds, xcd = h % kXcds, local = h / kXcds;
-  const uint32_t L = xcd < rem ? xcd * (q + 1) + local : rem * (q + 1) + (xcd - rem) * q + local;
-  const int n_tiles = tiles_m * tiles_n;
-  int t = (int)L;
-  if (t >= n_tiles) return;   // the whole workgroup leaves together
-  __shared__ __attribute__((aligned(16))) float As[2][LA::kLds];
-  __shared__ __attribute__((aligned(16))) float Bs[2][LB::kLds];
-  const int group = 8;        // grouped tile order, as in gemm_kernel
-  const int per_group = group * tiles_n;
-  auto origin = [&](int tt, int64_t& m0, int64_t& n0) {
-    const int g = tt / per_group;
-    const int first_m = g * group;
-    const int gsize = min(tiles_m - first_m, group);
-    m0 = (int64_t)(first_m + (tt % per_group) % gsize) * BM;
-    n0 = (int64_t)((tt % per_group) / gsize) * BN;
-  };
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int wm = wave % WM, wn = wave / WM;
-  const int half = lane >> 5;
-  const int li = lane & 31;
-  int64_t m0, n0;
-  origin(t, m0, n0);
-  la.init(m0, M);
-  lb.init(n0, N);
-  float4 ra[LA::kN], rb[LB::kN];
-  la.fetch(0, K, ra);
-  lb.fetch(0, K, rb);
-  LA::store(As[0], ra);
-  LB::store(Bs[0], rb);
-  __syncthreads();
-  int buf = 0;
-  while (true) {
-    floatx16 acc[MB][NB];
-#pragma unroll
-    for (int a = 0; a < MB; ++a)
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-    for (int64_t k0 = 0; k0 + BK < K; k0 += BK) {
-      la.fetch(k0 + BK, K, ra);
-      lb.fetch(k0 + BK, K, rb);
-      mma_ktile<BM, BN, LA, LB>(acc, As[buf], Bs[buf], wm, wn, half, li);
-      interleave_loads<LA::kN + LB::kN>();
-      LA::store(As[buf ^ 1], ra);
-      LB::store(Bs[buf ^ 1], rb);
-      __syncthreads();
-      buf ^= 1;
-    }
-    // the last K tile; the next output tile's first K tile is loaded meanwhile
-    // into the other buffer, which no wave reads until the barrier below
-    const int tn = t + (int)G;
-    const bool more = tn < n_tiles;   // uniform over the workgroup
-    int64_t m1 = 0, n1 = 0;
-    if (more) {
-      origin(tn, m1, n1);
-      la.init(m1, M);
-      lb.init(n1, N);
-      la.fetch(0, K, ra);
-      lb.fetch(0, K, rb);
-    }
-    mma_ktile<BM, BN, LA, LB>(acc, As[buf], Bs[buf], wm, wn, half, li);
-    if (more) {
-      LA::store(As[buf ^ 1], ra);
-      LB::store(Bs[buf ^ 1], rb);
-    }
-    store_tile<BM, BN, OM, BIAS>(acc, c, om, bias, m0, n0, M, N, wm, wn, half, li);
-    if (!more) break;
-    __syncthreads();
-    buf ^= 1;
-    t = tn;
-    m0 = m1;
-    n0 = n1;
-  }
-}
-
-// Loaders the persistent form is used with: the plain matrix views.
-template <class L> struct DenseView : std::false_type {};
-template <int E, bool V> struct DenseView<MatK<E, V>> : std::true_type {};
-template <int E, bool V> struct DenseView<MatM<E, V>> : std::true_type {};
-constexpr int64_t kShortK = 128;   // reductions at most this long run persistent
 
 template <int BM, int BN, class LA, class LB, class OM, bool BIAS, bool BATCHED = false,
           bool ROWSUM = false>
@@ -828,27 +987,6 @@ hipError_t run_gemm(const LA& la, const LB& lb, float* c, OM om, int64_t slice_s
   int64_t k_slice = (K + slices - 1) / slices;
   k_slice = (k_slice + BK - 1) / BK * BK;
   if (ROWSUM != (rowsum != nullptr)) return hipErrorInvalidValue;
-  if constexpr (!BATCHED && !ROWSUM && DenseView<LA>::value && DenseView<LB>::value) {
-    if (slices == 1 && K <= kShortK) {
-      // one workgroup per resident slot (the occupancy query counts LDS and registers)
-      auto kern = gemm_persistent<BM, BN, LA, LB, OM, BIAS>;
-      static const int64_t slots = [&] {   // initialised once, thread-safe
-        int o = 0, n = 0, dev = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, kern, THREADS, 0) != hipSuccess ||
-            o < 1)
-          o = 1;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            n < 1)
-          n = 256;
-        return (int64_t)o * n;
-      }();
-      const int64_t G = std::min<int64_t>(tiles_m * tiles_n, slots);
-      hipLaunchKernelGGL(kern, dim3((unsigned)G), dim3(THREADS), 0, s, la, lb, c, om, bias, M, N,
-                         K, (int)tiles_m, (int)tiles_n);
-      return hipGetLastError();
-    }
-  }
   dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)slices, (unsigned)batches);
   hipLaunchKernelGGL((gemm_kernel<BM, BN, LA, LB, OM, BIAS, BATCHED, ROWSUM>), grid, dim3(THREADS), 0, s,
                      la, lb, c, om, slice_stride, bias, M, N, K, k_slice, (int)tiles_m,
@@ -856,29 +994,41 @@ hipError_t run_gemm(const LA& la, const LB& lb, float* c, OM om, int64_t slice_s
   return hipGetLastError();
 }
 
-bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
-
-// Tile shape: 128 x 128, or 64 along a dimension that is at most 64 wide
-// (half of a 128-wide tile would compute zeros).  At most 64 columns and many
-// rows (the 64-channel convolutions) take 256 x 64: each wave then owns 64 x 64
-// and one round of LDS reads feeds 16 MFMAs instead of 8 (2-3 % faster
-// measured; plain, unbatched products only, to keep the kernel count down).
-// A product with fewer 128 x 128 tiles than half the CUs and a reduction of at
-// most 4096 (a dense layer at a small batch) takes 64 x 64 tiles, four times
-// as many workgroups, each wave one MFMA block.  Longer reductions keep
-// 128 x 128: those of few tiles are weight gradients, which split their rows
-// into slices instead.  Unbatched products only: a batched product has
-// workgroups enough across its batch.
-constexpr int64_t kTallRows = 65536;
-constexpr int64_t kFewTiles = 128;
-constexpr int64_t kFewTilesMaxK = 4096;
+// Tile shape of a product with `copies` batches or slices: the one of least
+// modelled time.  A CU takes k = ceil(tiles / CUs) tiles, up to `resident` of
+// them side by side (LDS and registers bound it); n side by side run at rate[n]
+// of what two 128 x 128 tiles reach together, so smaller tiles only pay where
+// the large ones leave CUs idle or alone.  Rates measured on convolutions and
+// dense products from 32 x 256 x 256 to 12288 x 4096 x 1024, each run with
+// every shape.
 enum Shape { S128x128, S128x64, S64x128, S256x64, S64x64 };
-Shape pick_shape(int64_t M, int64_t N, int64_t K) {
-  if (N <= 64 && M >= kTallRows) return S256x64;
-  if (N <= 64 && M > 64) return S128x64;
-  if (M <= 64) return S64x128;
-  if (((M + 127) / 128) * ((N + 127) / 128) < kFewTiles && K <= kFewTilesMaxK) return S64x64;
-  return S128x128;
+struct ShapeRate {
+  int bm, bn, resident;
+  double rate[6];   // [n - 1], n tiles side by side
+};
+constexpr ShapeRate kShapes[] = {
+    {128, 128, 2, {0.72, 1.0}},
+    {128, 64, 3, {0.52, 0.74, 0.84}},
+    {64, 128, 3, {0.51, 0.73, 0.83}},
+    {256, 64, 2, {0.66, 0.92}},
+    {64, 64, 5, {0.36, 0.54, 0.60, 0.63, 0.78}},
+};
+double shape_time(const ShapeRate& r, int64_t M, int64_t N, int64_t copies) {
+  constexpr int64_t kCUs = 256;
+  const int64_t tiles = ((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn) * copies;
+  const int64_t k = (tiles + kCUs - 1) / kCUs, rem = k % r.resident;
+  return r.bm * r.bn * ((k - rem) / r.rate[r.resident - 1] + (rem ? rem / r.rate[rem - 1] : 0.0));
+}
+// K is the reduction of one copy.  256 x 64 tiles are for at most 64 columns
+// and long reductions (64-channel 3 x 3 convolutions: 6 % faster than 128 x 64
+// at K = 576, 10 % slower at K = 256).
+Shape pick_shape(int64_t M, int64_t N, int64_t K, int64_t copies) {
+  int best = S128x128;
+  for (int i = S128x64; i <= S64x64; ++i) {
+    if (i == S256x64 && (N > 64 || K < 512)) continue;
+    if (shape_time(kShapes[i], M, N, copies) < shape_time(kShapes[best], M, N, copies)) best = i;
+  }
+  return (Shape)best;
 }
 
 // Runs the GEMM with loader templates A<E>, B<E> instantiated for the chosen
@@ -890,15 +1040,15 @@ hipError_t dispatch(FA fa, FB fb, float* c, OM om, int64_t slice_stride, const f
                     int64_t M, int64_t N, int64_t K, int64_t slices, hipStream_t s,
                     int64_t batches = 1, Batch bt = Batch{1, 0, 0, 0, 0, 0, 0, 0},
                     float* rowsum = nullptr) {
-  switch (pick_shape(M, N, K)) {
+  switch (pick_shape(M, N, K / slices, slices * batches)) {
     case S256x64:
-      if constexpr (!BATCHED && !ROWSUM) {
+      if constexpr (!BATCHED) {
         LAT<256> a{};
         LBT<64> b{};
         fa(a);
         fb(b);
-        return run_gemm<256, 64, LAT<256>, LBT<64>, OM, BIAS, false, false>(
-            a, b, c, om, slice_stride, bias, M, N, K, slices, s);
+        return run_gemm<256, 64, LAT<256>, LBT<64>, OM, BIAS, false, ROWSUM>(
+            a, b, c, om, slice_stride, bias, M, N, K, slices, s, 1, bt, rowsum);
       }
       [[fallthrough]];
     case S128x64: {
@@ -918,13 +1068,13 @@ hipError_t dispatch(FA fa, FB fb, float* c, OM om, int64_t slice_stride, const f
           a, b, c, om, slice_stride, bias, M, N, K, slices, s, batches, bt, rowsum);
     }
     case S64x64:
-      if constexpr (!BATCHED) {
+      if constexpr (true) {
         LAT<64> a{};
         LBT<64> b{};
         fa(a);
         fb(b);
-        return run_gemm<64, 64, LAT<64>, LBT<64>, OM, BIAS, false, ROWSUM>(
-            a, b, c, om, slice_stride, bias, M, N, K, slices, s, 1, bt, rowsum);
+        return run_gemm<64, 64, LAT<64>, LBT<64>, OM, BIAS, BATCHED, ROWSUM>(
+            a, b, c, om, slice_stride, bias, M, N, K, slices, s, batches, bt, rowsum);
       }
       [[fallthrough]];
     default: {
@@ -962,10 +1112,6 @@ hipError_t dispatch_shape(FA fa, FB fb, float* c, OM om, int64_t slice_stride, i
                                                        slices, s);
 }
 
-template <int E> using MatKv = MatK<E, true>;
-template <int E> using MatKs = MatK<E, false>;
-template <int E> using MatMv = MatM<E, true>;
-template <int E> using MatMs = MatM<E, false>;
 template <int E> using ConvPatchT = ConvPatch<E, TAP>;
 template <int E> using ConvPatchV = ConvPatch<E, VEC4>;
 template <int E> using ConvPatchS = ConvPatch<E, SCALAR>;
@@ -974,12 +1120,11 @@ template <int E> using ConvGradTapV = ConvGradTap<E, VEC4>;
 template <int E> using ConvGradTapS = ConvGradTap<E, SCALAR>;
 template <int E> using ConvFilterTapT = ConvFilterTap<E, TAP>;
 template <int E> using ConvFilterTapG = ConvFilterTap<E, VEC4>;
-template <int E> using ConvPixelPatchT = ConvPixelPatch<E, TAP>;
 template <int E> using ConvPixelPatchV = ConvPixelPatch<E, VEC4>;
 template <int E> using ConvPixelPatchS = ConvPixelPatch<E, SCALAR>;
 
 // the GEMM sizes of the convolution views index with 32-bit arithmetic
-bool fits31(int64_t v) { return v >= 0 && v < (int64_t(1) << 31) - 64; }
+bool fits31(int64_t v) { return v >= 0 && v < (int64_t(1) << 31) - 512; }
 
 // Tile of a filter gradient (M = output channels, N = RSC), first rule that
 // applies; the lowering's split-K slice count follows the same rule:
@@ -1068,23 +1213,40 @@ hipError_t class_zero(float* dx, const ClassOut& om, int64_t M, int64_t C, hipSt
 }  // namespace
 
 // ---------------------------------------------------------------- launchers
+namespace {
+// Fills a dense view
+auto dense(const float* p, int64_t ld, int64_t kdim) {
+  return [=](auto& l) { l.p = p; l.ld = ld; l.kdim = kdim; };
+}
+
+// Whether the bytes between the first image row and the last that `pixels`
+// consecutive pixels of an (N, rows, cols) grid can touch fit a buffer
+// descriptor: pixel (h, w) reads rows h st + [-back, taps) of (imgH, imgW, C)
+// images.
+bool window_fits(int64_t pixels, int64_t rows, int64_t cols, int64_t st, int64_t taps,
+                 int64_t imgH, int64_t imgW, int64_t C) {
+  const int64_t lines = (pixels + cols - 1) / cols + 1;          // grid rows touched
+  const int64_t images = (lines + rows - 1) / rows + 1;          // images touched
+  const int64_t skip = std::max<int64_t>(0, imgH - (rows - 1) * st);   // at each change of image
+  const int64_t span = std::min(images * imgH, lines * st + taps + images * (skip + taps));
+  return span < (int64_t(1) << 29) / C / imgW;
+}
+}  // namespace
+
 hipError_t linear_fwd(const float* X, const float* W, const float* b, float* Y, int64_t M,
                       int64_t K, int64_t N, hipStream_t s) {
-  auto fa = [&](auto& a) { a.p = X; a.ld = K; };
-  auto fb = [&](auto& bb) { bb.p = W; bb.ld = K; };
-  if (K % 4 == 0 && aligned16(X) && aligned16(W))
-    return dispatch_dense<MatKv, MatKv, true>(fa, fb, Y, N, b, M, N, K, 1, s);
-  return dispatch_dense<MatKs, MatKs, true>(fa, fb, Y, N, b, M, N, K, 1, s);
+  const auto fa = dense(X, K, K), fb = dense(W, K, K);
+  if (K <= kMaxLd) return dispatch_dense<MatK, MatK, true>(fa, fb, Y, N, b, M, N, K, 1, s);
+  return dispatch_dense<MatKFar, MatKFar, true>(fa, fb, Y, N, b, M, N, K, 1, s);
 }
 
 hipError_t linear_bwd_x(const float* W, const float* dY, float* dX, int64_t M, int64_t K,
                         int64_t N, hipStream_t s) {
   // dX[M][K] = dY[M][N] W[N][K]: A = dY (contiguous along the reduction), B[n_out][k_in] = W
-  auto fa = [&](auto& a) { a.p = dY; a.ld = N; };
-  auto fb = [&](auto& bb) { bb.p = W; bb.ld = K; };
-  if (N % 4 == 0 && K % 4 == 0 && aligned16(W) && aligned16(dY))
-    return dispatch_dense<MatKv, MatMv, false>(fa, fb, dX, K, nullptr, M, K, N, 1, s);
-  return dispatch_dense<MatKs, MatMs, false>(fa, fb, dX, K, nullptr, M, K, N, 1, s);
+  const auto fa = dense(dY, N, N), fb = dense(W, K, N);
+  if (std::max(N, K) <= kMaxLd)
+    return dispatch_dense<MatK, MatM, false>(fa, fb, dX, K, nullptr, M, K, N, 1, s);
+  return dispatch_dense<MatKFar, MatMFar, false>(fa, fb, dX, K, nullptr, M, K, N, 1, s);
 }
 
 hipError_t linear_bwd_w(const float* X, const float* dY, float* dW, float* db, float* part,
@@ -1094,16 +1256,15 @@ hipError_t linear_bwd_w(const float* X, const float* dY, float* dW, float* db, f
   if (slices > 1 && part == nullptr) return hipErrorInvalidValue;
   float* out = slices > 1 ? part : dW;
   float* sums = slices > 1 ? part + slices * N * K : db;
-  auto fa = [&](auto& a) { a.p = dY; a.ld = N; };
-  auto fb = [&](auto& bb) { bb.p = X; bb.ld = K; };
+  const auto fa = dense(dY, N, M), fb = dense(X, K, M);
   const Batch one{1, 0, 0, 0, 0, 0, 0};
   hipError_t e;
-  if (N % 4 == 0 && K % 4 == 0 && aligned16(X) && aligned16(dY))
-    e = dispatch_dense<MatMv, MatMv, false, false, true>(fa, fb, out, K, nullptr, N, K, M, slices,
-                                                         s, 1, one, sums);
+  if (std::max(N, K) <= kMaxLd)
+    e = dispatch_dense<MatM, MatM, false, false, true>(fa, fb, out, K, nullptr, N, K, M, slices, s,
+                                                       1, one, sums);
   else
-    e = dispatch_dense<MatMs, MatMs, false, false, true>(fa, fb, out, K, nullptr, N, K, M, slices,
-                                                         s, 1, one, sums);
+    e = dispatch_dense<MatMFar, MatMFar, false, false, true>(fa, fb, out, K, nullptr, N, K, M,
+                                                             slices, s, 1, one, sums);
   if (e != hipSuccess || slices <= 1) return e;
   e = slice_sum(part, dW, N * K, slices, s);
   if (e != hipSuccess) return e;
@@ -1115,24 +1276,19 @@ hipError_t gemm_batched(bool a_rowk, const float* A, int64_t lda, bool b_rowk, c
                         int64_t batches, const BatchStrides& st, hipStream_t s) {
   const Batch bt{st.inner,   st.a_outer, st.a_inner, st.b_outer,
                  st.b_inner, st.c_outer, st.c_inner, st.skip_upper};
-  auto fa = [&](auto& a) { a.p = A; a.ld = lda; };
-  auto fb = [&](auto& b) { b.p = B; b.ld = ldb; };
-  const bool vec = lda % 4 == 0 && ldb % 4 == 0 && aligned16(A) && aligned16(B) &&
-                   (a_rowk ? K % 4 == 0 : M % 4 == 0) && (b_rowk ? K % 4 == 0 : N % 4 == 0) &&
-                   st.a_outer % 4 == 0 && st.a_inner % 4 == 0 && st.b_outer % 4 == 0 &&
-                   st.b_inner % 4 == 0;
+  const auto fa = dense(A, lda, K), fb = dense(B, ldb, K);
 #define GEMM_BATCHED_CASE(LA, LB) \
   return dispatch_dense<LA, LB, false, true>(fa, fb, C, ldc, nullptr, M, N, K, 1, s, batches, bt)
-  if (vec) {
-    if (a_rowk && b_rowk) GEMM_BATCHED_CASE(MatKv, MatKv);
-    if (a_rowk) GEMM_BATCHED_CASE(MatKv, MatMv);
-    if (b_rowk) GEMM_BATCHED_CASE(MatMv, MatKv);
-    GEMM_BATCHED_CASE(MatMv, MatMv);
+  if (std::max(lda, ldb) <= kMaxLd) {
+    if (a_rowk && b_rowk) GEMM_BATCHED_CASE(MatK, MatK);
+    if (a_rowk) GEMM_BATCHED_CASE(MatK, MatM);
+    if (b_rowk) GEMM_BATCHED_CASE(MatM, MatK);
+    GEMM_BATCHED_CASE(MatM, MatM);
   }
-  if (a_rowk && b_rowk) GEMM_BATCHED_CASE(MatKs, MatKs);
-  if (a_rowk) GEMM_BATCHED_CASE(MatKs, MatMs);
-  if (b_rowk) GEMM_BATCHED_CASE(MatMs, MatKs);
-  GEMM_BATCHED_CASE(MatMs, MatMs);
+  if (a_rowk && b_rowk) GEMM_BATCHED_CASE(MatKFar, MatKFar);
+  if (a_rowk) GEMM_BATCHED_CASE(MatKFar, MatMFar);
+  if (b_rowk) GEMM_BATCHED_CASE(MatMFar, MatKFar);
+  GEMM_BATCHED_CASE(MatMFar, MatMFar);
 #undef GEMM_BATCHED_CASE
 }
 
@@ -1141,55 +1297,51 @@ hipError_t gemm_batched(bool a_rowk, const float* A, int64_t lda, bool b_rowk, c
 // gradient dY^T X, all run on the dense loaders (one add per K tile for the
 // address, no tap arithmetic).
 static bool pointwise(const ConvShape& c) {
-  return c.R == 1 && c.S == 1 && c.stride == 1 && c.pad == 0 && c.C % 4 == 0 && c.K % 4 == 0;
+  return c.R == 1 && c.S == 1 && c.stride == 1 && c.pad == 0 && c.C <= kMaxLd && c.K <= kMaxLd;
 }
 
 hipError_t conv_fwd(const float* X, const float* W, float* Y, const ConvShape& c, hipStream_t s) {
   const int64_t M = c.N * c.P * c.Q, N = c.K, K = c.R * c.S * c.C;
   if (!fits31(M) || !fits31(K)) return hipErrorInvalidValue;
-  if (pointwise(c) && N > 32 && aligned16(X) && aligned16(W)) {
-    // Y[NPQ][K] = X[NPQ][C] W[K][C]^T
-    auto fa = [&](auto& a) { a.p = X; a.ld = c.C; };
-    auto fb = [&](auto& b) { b.p = W; b.ld = c.C; };
-    return dispatch_dense<MatKv, MatKv, false>(fa, fb, Y, N, nullptr, M, N, K, 1, s);
-  }
+  if (pointwise(c) && N > 32)   // Y[NPQ][K] = X[NPQ][C] W[K][C]^T
+    return dispatch_dense<MatK, MatK, false>(dense(X, c.C, K), dense(W, c.C, K), Y, N, nullptr, M,
+                                             N, K, 1, s);
   auto fa = [&](auto& a) {
     a.x = X; a.H = (int)c.H; a.W = (int)c.W; a.C = (int)c.C; a.S = (int)c.S;
     a.st = (int)c.stride; a.pad = (int)c.pad;
     a.dQ = FastDiv::make(c.Q); a.dPQ = FastDiv::make(c.P * c.Q); a.dC = FastDiv::make(c.C);
     a.dS = FastDiv::make(c.S); a.dSC = FastDiv::make(c.S * c.C);
   };
-  auto fb = [&](auto& b) { b.p = W; b.ld = K; };
-  if (N <= 32 && c.C % 4 == 0) {
+  const auto fb = dense(W, K, K);
+  const bool near = c.C % 4 == 0 && K <= kMaxLd &&
+                    window_fits(256, c.P, c.Q, c.stride, c.R + 2 * c.pad, c.H, c.W, c.C);
+  if (N <= 32 && near) {
     // at most 32 output channels: 256 x 32 tiles, no empty columns; 128 x 32 when there are
     // fewer 256-row tiles than CUs, so that twice as many workgroups share the chip
     if ((M + 255) / 256 < 256) {
       if (c.C % 32 == 0)
-        return dispatch_shape<128, 32, ConvPatchT, MatKv>(fa, fb, Y, DenseOut{N}, 0, M, N, K, 1, s);
-      return dispatch_shape<128, 32, ConvPatchV, MatKv>(fa, fb, Y, DenseOut{N}, 0, M, N, K, 1, s);
+        return dispatch_shape<128, 32, ConvPatchT, MatK>(fa, fb, Y, DenseOut{N}, 0, M, N, K, 1, s);
+      return dispatch_shape<128, 32, ConvPatchV, MatK>(fa, fb, Y, DenseOut{N}, 0, M, N, K, 1, s);
     }
     if (c.C % 32 == 0)
-      return dispatch_shape<256, 32, ConvPatchT, MatKv>(fa, fb, Y, DenseOut{N}, 0, M, N, K, 1, s);
-    return dispatch_shape<256, 32, ConvPatchV, MatKv>(fa, fb, Y, DenseOut{N}, 0, M, N, K, 1, s);
+      return dispatch_shape<256, 32, ConvPatchT, MatK>(fa, fb, Y, DenseOut{N}, 0, M, N, K, 1, s);
+    return dispatch_shape<256, 32, ConvPatchV, MatK>(fa, fb, Y, DenseOut{N}, 0, M, N, K, 1, s);
   }
-  if (c.C % 32 == 0)
-    return dispatch_dense<ConvPatchT, MatKv, false>(fa, fb, Y, N, nullptr, M, N, K, 1, s);
-  if (c.C % 4 == 0)
-    return dispatch_dense<ConvPatchV, MatKv, false>(fa, fb, Y, N, nullptr, M, N, K, 1, s);
-  return dispatch_dense<ConvPatchS, MatKs, false>(fa, fb, Y, N, nullptr, M, N, K, 1, s);
+  if (near && c.C % 32 == 0)
+    return dispatch_dense<ConvPatchT, MatK, false>(fa, fb, Y, N, nullptr, M, N, K, 1, s);
+  if (near) return dispatch_dense<ConvPatchV, MatK, false>(fa, fb, Y, N, nullptr, M, N, K, 1, s);
+  if (K <= kMaxLd)
+    return dispatch_dense<ConvPatchS, MatK, false>(fa, fb, Y, N, nullptr, M, N, K, 1, s);
+  return dispatch_dense<ConvPatchS, MatKFar, false>(fa, fb, Y, N, nullptr, M, N, K, 1, s);
 }
 
 hipError_t conv_bwd_x(const float* W, const float* dY, float* dX, const ConvShape& c,
                       hipStream_t s) {
   if (c.C % 4 != 0) return hipErrorInvalidValue;   // every conv with an input gradient has C % 4 == 0
   if (!fits31(c.N * c.H * c.W) || !fits31(c.R * c.S * c.K)) return hipErrorInvalidValue;
-  if (pointwise(c) && aligned16(W) && aligned16(dY)) {
-    // dX[NHW][C] = dY[NHW][K] W[K][C]
-    auto fa = [&](auto& a) { a.p = dY; a.ld = c.K; };
-    auto fb = [&](auto& b) { b.p = W; b.ld = c.C; };
-    return dispatch_dense<MatKv, MatMv, false>(fa, fb, dX, c.C, nullptr, c.N * c.H * c.W, c.C, c.K,
-                                               1, s);
-  }
+  if (pointwise(c))   // dX[NHW][C] = dY[NHW][K] W[K][C]
+    return dispatch_dense<MatK, MatM, false>(dense(dY, c.K, c.K), dense(W, c.C, c.K), dX, c.C,
+                                             nullptr, c.N * c.H * c.W, c.C, c.K, 1, s);
   const int64_t st = c.stride;
   // one GEMM per stride class (ph, pw) of input pixels; a class no tap reaches gets zeros
   for (int64_t ph = 0; ph < st; ++ph)
@@ -1200,9 +1352,10 @@ hipError_t conv_bwd_x(const float* W, const float* dY, float* dX, const ConvShap
       const int64_t nS = s0 < c.S ? (c.S - s0 + st - 1) / st : 0;
       const int64_t M = c.N * Hc * Wc, N = c.C, K = nR * nS * c.K;
       if (M == 0) continue;
+      const int64_t up = (ph + c.pad - r0) / st;   // rows of dY above the class pixel's own
       auto fa = [&](auto& a) {
-        a.dy = dY; a.P = (int)c.P; a.Q = (int)c.Q; a.K = (int)c.K; a.nS = (int)nS;
-        a.a = (int)((ph + c.pad - r0) / st); a.b = (int)((pw + c.pad - s0) / st);
+        a.dy = dY; a.P = (int)c.P; a.Q = (int)c.Q; a.K = (int)c.K; a.nR = (int)nR; a.nS = (int)nS;
+        a.a = (int)up; a.b = (int)((pw + c.pad - s0) / st);
         a.dWc = FastDiv::make(Wc); a.dHWc = FastDiv::make(Hc * Wc); a.dK = FastDiv::make(c.K);
         a.dnS = FastDiv::make(nS > 0 ? nS : 1); a.dSK = FastDiv::make(nS > 0 ? nS * c.K : 1);
       };
@@ -1214,13 +1367,15 @@ hipError_t conv_bwd_x(const float* W, const float* dY, float* dX, const ConvShap
       };
       const ClassOut om{(int)c.H, (int)c.W, (int)c.C, (int)st, (int)ph, (int)pw,
                         FastDiv::make(Wc), FastDiv::make(Hc * Wc)};
+      const bool near = c.K % 4 == 0 &&
+                        window_fits(256, Hc, Wc, 1, nR + 2 * up + 1, c.P, c.Q, c.K);
       hipError_t e;
-      if (K == 0 && aligned16(dX))   // no tap: a plain fill instead of an empty product
+      if (K == 0)   // no tap: a plain fill instead of an empty product
         e = class_zero(dX, om, M, c.C, s);
-      else if (c.K % 32 == 0)
+      else if (near && c.K % 32 == 0 && c.R * c.S * c.C <= kMaxLd)
         e = dispatch<ConvGradTapT, ConvFilterTapT, false>(fa, fb, dX, om, 0, nullptr, M, N, K, 1,
                                                           s);
-      else if (c.K % 4 == 0)
+      else if (near)
         e = dispatch<ConvGradTapV, ConvFilterTapG, false>(fa, fb, dX, om, 0, nullptr, M, N, K, 1,
                                                           s);
       else
@@ -1238,53 +1393,37 @@ hipError_t conv_bwd_w(const float* X, const float* dY, float* dW, float* part, i
   if (!fits31(K) || !fits31(N) || !fits31((c.R * c.W + c.S) * c.C)) return hipErrorInvalidValue;
   if (slices > 1 && part == nullptr) return hipErrorInvalidValue;
   float* out = slices > 1 ? part : dW;
-  auto fa = [&](auto& a) { a.p = dY; a.ld = c.K; };
+  const auto fa = dense(dY, c.K, K);
   auto fb = [&](auto& b) {
     b.x = X; b.H = (int)c.H; b.W = (int)c.W; b.C = (int)c.C; b.st = (int)c.stride;
-    b.pad = (int)c.pad; b.dQ = FastDiv::make(c.Q); b.dPQ = FastDiv::make(c.P * c.Q);
+    b.pad = (int)c.pad; b.h_end = (int)(c.P * c.stride - c.pad);
+    b.w_end = (int)(c.Q * c.stride - c.pad);
+    b.row_step = c.stride * (c.W - c.Q) * c.C;
+    b.img_step = (c.H - c.P * c.stride) * c.W * c.C;
+    b.dQ = FastDiv::make(c.Q); b.dPQ = FastDiv::make(c.P * c.Q);
     b.dC = FastDiv::make(c.C); b.dSC = FastDiv::make(c.S * c.C);
   };
   const DenseOut om{N};
+  // a K tile covers 32 pixels; twice that covers the offsets of a lane's steps past the tile
+  const bool near = c.C % 4 == 0 && c.K <= kMaxLd &&
+                    window_fits(64, c.P, c.Q, c.stride, c.R + 2 * c.pad, c.H, c.W, c.C);
+  const WgradTile tile = wgrad_tile(M, N, c.C);
   hipError_t e;
-  switch (wgrad_tile(M, N, c.C)) {
-    case WgradTile::k32x256:   // at most 32 output channels: no empty tile rows
-      e = c.C % 32 == 0
-              ? dispatch_shape<32, 256, MatMv, ConvPixelPatchT>(fa, fb, out, om, M * N, M, N, K,
-                                                                slices, s)
-              : dispatch_shape<32, 256, MatMv, ConvPixelPatchV>(fa, fb, out, om, M * N, M, N, K,
-                                                                slices, s);
-      break;
-    case WgradTile::k64x192:   // no tile column half empty when RSC is an odd multiple of 64
-      e = dispatch_shape<64, 192, MatMv, ConvPixelPatchV>(fa, fb, out, om, M * N, M, N, K, slices,
-                                                          s);
-      break;
-    case WgradTile::k64x64:    // RSC of at most 64 (1 x 1 filters, the 3-channel first layer)
-      e = c.C % 16 == 0 ? dispatch_shape<64, 64, MatMv, ConvPixelPatchT>(fa, fb, out, om, M * N, M,
-                                                                         N, K, slices, s)
-          : c.C % 4 == 0 ? dispatch_shape<64, 64, MatMv, ConvPixelPatchV>(fa, fb, out, om, M * N,
-                                                                          M, N, K, slices, s)
-                         : dispatch_shape<64, 64, MatMv, ConvPixelPatchS>(fa, fb, out, om, M * N,
-                                                                          M, N, K, slices, s);
-      break;
-    default:
-      if (pointwise(c) && aligned16(X) && aligned16(dY)) {
-        // dW[K][C] = dY^T X over the pixel rows: the dense weight gradient's loaders (the same
-        // tile shapes as the general case below, so the slice count is the same)
-        auto fx = [&](auto& b) { b.p = X; b.ld = c.C; };
-        e = dispatch_dense<MatMv, MatMv, false>(fa, fx, out, N, nullptr, M, N, K, slices, s);
-      } else if (c.K % 4 != 0)
-        e = dispatch_dense<MatMs, ConvPixelPatchS, false>(fa, fb, out, N, nullptr, M, N, K, slices,
-                                                          s);
-      else if (c.C % 16 == 0)
-        e = dispatch_dense<MatMv, ConvPixelPatchT, false>(fa, fb, out, N, nullptr, M, N, K, slices,
-                                                          s);
-      else if (c.C % 4 == 0)
-        e = dispatch_dense<MatMv, ConvPixelPatchV, false>(fa, fb, out, N, nullptr, M, N, K, slices,
-                                                          s);
-      else
-        e = dispatch_dense<MatMv, ConvPixelPatchS, false>(fa, fb, out, N, nullptr, M, N, K, slices,
-                                                          s);
-  }
+  if (near && tile == WgradTile::k32x256)   // at most 32 output channels: no empty tile rows
+    e = dispatch_shape<32, 256, MatM, ConvPixelPatchV>(fa, fb, out, om, M * N, M, N, K, slices, s);
+  else if (near && tile == WgradTile::k64x192)   // no tile column half empty at odd multiples of 64
+    e = dispatch_shape<64, 192, MatM, ConvPixelPatchV>(fa, fb, out, om, M * N, M, N, K, slices, s);
+  else if (pointwise(c))
+    // dW[K][C] = dY^T X over the pixel rows: the dense weight gradient's loaders
+    e = dispatch_dense<MatM, MatM, false>(fa, dense(X, c.C, K), out, N, nullptr, M, N, K, slices,
+                                          s);
+  else if (near)
+    e = dispatch_dense<MatM, ConvPixelPatchV, false>(fa, fb, out, N, nullptr, M, N, K, slices, s);
+  else if (c.K <= kMaxLd)
+    e = dispatch_dense<MatM, ConvPixelPatchS, false>(fa, fb, out, N, nullptr, M, N, K, slices, s);
+  else
+    e = dispatch_dense<MatMFar, ConvPixelPatchS, false>(fa, fb, out, N, nullptr, M, N, K, slices,
+                                                        s);
   if (e != hipSuccess || slices <= 1) return e;
   return slice_sum(part, dW, M * N, slices, s);
 }
@@ -1299,7 +1438,7 @@ hipError_t conv_bwd_w(const float* X, const float* dY, float* dW, float* part, i
 // four rounds and at least 256 rows a slice; the smallest s within 1 % of the
 // best is taken, since every slice adds one partial dW to write and read back.
 int64_t wgrad_slices(int64_t M, int64_t N, int64_t K, int64_t C) {
-  constexpr int64_t kCUs = 256;
+  constexpr int64_t kCUs = 256, kFewTiles = 128, kFewTilesMaxK = 4096;
   int64_t tiles, resident;
   const WgradTile t = C >= 0 ? wgrad_tile(M, N, C) : WgradTile::kGeneral;
   if (t == WgradTile::k32x256) {
@@ -1309,13 +1448,17 @@ int64_t wgrad_slices(int64_t M, int64_t N, int64_t K, int64_t C) {
   } else if (t == WgradTile::k64x64) {
     tiles = 1, resident = C % 4 == 0 ? 5 : 4;
   } else {
-    switch (pick_shape(M, N, K)) {
-      case S256x64: tiles = (M + 255) / 256, resident = 2; break;
-      case S128x64: tiles = (M + 127) / 128, resident = 3; break;
-      case S64x128: tiles = (N + 127) / 128, resident = 3; break;
-      case S64x64: tiles = ((M + 63) / 64) * ((N + 63) / 64), resident = 4; break;
-      default: tiles = ((M + 127) / 128) * ((N + 127) / 128), resident = 2;
-    }
+    const int64_t large = ((M + 127) / 128) * ((N + 127) / 128);
+    if (N <= 64 && M >= 65536)
+      tiles = (M + 255) / 256, resident = 2;
+    else if (N <= 64 && M > 64)
+      tiles = (M + 127) / 128, resident = 3;
+    else if (M <= 64)
+      tiles = (N + 127) / 128, resident = 3;
+    else if (large < kFewTiles && K <= kFewTilesMaxK)
+      tiles = ((M + 63) / 64) * ((N + 63) / 64), resident = 4;
+    else
+      tiles = large, resident = 2;
   }
   const int64_t slots = kCUs * resident;
   const int64_t smax = std::max<int64_t>(1, std::min(4 * slots / tiles, (K + 255) / 256));

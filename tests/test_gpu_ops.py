@@ -104,6 +104,57 @@ def test_linear(M, K, N, S):
     assert rel_err(dX, ops.linear_bwd_x(d(Wt), d(G))) < TOL
 
 
+@pytest.mark.parametrize("kind", ["normal", "subnormal", "large", "special"])
+@pytest.mark.parametrize("M,K,N", [(70, 100, 66), (129, 33, 257), (1, 7, 3)])
+def test_linear_split_range(M, K, N, kind):
+    """The products of split operands hold over the whole fp32 range: subnormal inputs (times large
+    ones), sums past 2^48 and infinities or NaN, whose tiles are computed again by fp32 products.
+    Tolerance as for every single kernel, relative to the largest element of the finite ones."""
+    X, Wt, b, G = f32(M, K), f32(N, K), np.zeros(N, np.float32), f32(M, N)
+    if kind == "subnormal":
+        X, Wt, G = X * np.float32(1e-39), Wt * np.float32(1e20), G * np.float32(1e-40)
+    elif kind == "large":
+        X, Wt, G = X * np.float32(1e27), Wt * np.float32(1e9), G * np.float32(1e8)
+    elif kind == "special":
+        X[M // 2, K // 2], G[0, N - 1], Wt[N // 2, 0] = np.inf, np.nan, -np.inf
+
+    def same(got, ref):
+        fine = np.isfinite(ref)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)), kind
+        inf = np.isinf(ref)
+        assert np.array_equal(got[inf], ref[inf]), kind
+        assert fine.sum() == 0 or rel_err(got[fine], ref[fine]) < TOL, kind
+
+    with np.errstate(invalid="ignore"):
+        refs = (d(X) @ d(Wt).T, d(G).T @ d(X), d(G) @ d(Wt))
+    (_, _, _, Y) = run_fn("linear_fwd", [(X, ooc.R), (Wt, ooc.R), (b, ooc.R),
+                                          (((M, N), "f32"), ooc.W)], [M, K, N])
+    same(Y, refs[0])
+    dW = run_fn("linear_bwd_w", [(X, ooc.R), (G, ooc.R), (((N, K), "f32"), ooc.W),
+                                 (((N,), "f32"), ooc.W)], [M, K, N, 1])[2]
+    same(dW, refs[1])
+    (_, _, dX) = run_fn("linear_bwd_x", [(Wt, ooc.R), (G, ooc.R), (((M, K), "f32"), ooc.W)],
+                        [M, K, N])
+    same(dX, refs[2])
+
+
+def test_linear_far_rows():
+    """Rows of more than 2^21 values: the loaders with 64-bit addresses."""
+    M, K, N = 3, (1 << 21) + 5, 2
+    X, Wt, b, G = f32(M, K), f32(N, K), f32(N), f32(M, N)
+    (_, _, _, Y) = run_fn("linear_fwd", [(X, ooc.R), (Wt, ooc.R), (b, ooc.R),
+                                          (((M, N), "f32"), ooc.W)], [M, K, N], 2 << 20)
+    # a running fp32 sum of K terms errs by about sqrt(K) 2^-24 = 9e-5 of a result
+    assert rel_err(Y, ops.linear_fwd(d(X), d(Wt), d(b))) < 1e-4
+    dW, db = run_fn("linear_bwd_w", [(X, ooc.R), (G, ooc.R), (((N, K), "f32"), ooc.W),
+                                     (((N,), "f32"), ooc.W)], [M, K, N, 1], 2 << 20)[2:4]
+    rdW, rdb = ops.linear_bwd_w(d(X), d(G))
+    assert rel_err(dW, rdW) < TOL and rel_err(db, rdb) < TOL
+    (_, _, dX) = run_fn("linear_bwd_x", [(Wt, ooc.R), (G, ooc.R), (((M, K), "f32"), ooc.W)],
+                        [M, K, N], 2 << 20)
+    assert rel_err(dX, ops.linear_bwd_x(d(Wt), d(G))) < TOL
+
+
 # ---------------------------------------------------------------- conv
 CONVS = [  # N, H, W, C, K, k, stride, pad
     (2, 9, 9, 4, 8, 3, 1, 1),
