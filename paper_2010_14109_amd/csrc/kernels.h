@@ -55,6 +55,10 @@ hipError_t accumulate(float* a, const float* b, int64_t n, hipStream_t s);
 // count parameter tensors: w[k] -= lr * (v[k] = mu v[k] + g[k]), or lr * g[k] where v[k] is null
 hipError_t sgd(int count, float* const* w, const float* const* g, float* const* v,
                const int64_t* n, float lr, float mu, hipStream_t s);
+// count copies between device memory and mapped (pinned) host memory, each at 16-byte aligned
+// addresses
+hipError_t copy_many(int count, void* const* dst, const void* const* src, const uint64_t* bytes,
+                     hipStream_t s);
 hipError_t softmax_ce(const float* logits, const int32_t* labels, float* loss, float* dlogits,
                       int64_t N, int64_t classes, hipStream_t s);
 hipError_t bn_fwd(const float* x, const float* gamma, const float* beta, float* y, float* stats,

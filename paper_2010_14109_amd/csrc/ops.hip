@@ -126,6 +126,34 @@ __global__ void sgd_kernel(SgdSet set, float lr, float mu) {
   }
 }
 
+// ---------------------------------------------------------------- many copies
+// Up to kCopySet buffers between device memory and pinned host memory in one
+// launch; a workgroup moves kCopyBlock bytes of the buffer whose block range
+// holds it.  Bound by the host link; a copy call of its own costs about 15 us
+// however small, and a network has hundreds of variables of a few KiB.
+constexpr int kCopySet = 64;
+constexpr uint32_t kCopyBlock = 16384;
+struct CopySet {
+  char* dst[kCopySet];
+  const char* src[kCopySet];
+  uint64_t bytes[kCopySet];
+  uint32_t first[kCopySet + 1];   // first workgroup of each buffer
+  int n;
+};
+
+__global__ __launch_bounds__(TPB) void copy_kernel(CopySet set) {
+  int k = 0;
+  while (k + 1 < set.n && set.first[k + 1] <= blockIdx.x) ++k;   // uniform
+  const uint64_t at = (uint64_t)(blockIdx.x - set.first[k]) * kCopyBlock;
+  const uint64_t end = min(set.bytes[k], at + kCopyBlock);
+  char* __restrict__ d = set.dst[k];
+  const char* __restrict__ s = set.src[k];
+  uint64_t i = at + 16 * threadIdx.x;
+  for (; i + 16 <= end; i += 16 * TPB)
+    *reinterpret_cast<float4*>(d + i) = *reinterpret_cast<const float4*>(s + i);
+  for (; i < end; ++i) d[i] = s[i];   // the lane of the last partial 16 bytes
+}
+
 // ---------------------------------------------------------------- softmax cross-entropy
 __device__ inline float wave_max(float x) {
   for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
@@ -800,6 +828,27 @@ hipError_t add(const float* a, const float* b, float* y, int64_t n, hipStream_t 
   return ew<2>(a, b, y, n, s);
 }
 
+hipError_t copy_many(int count, void* const* dst, const void* const* src, const uint64_t* bytes,
+                     hipStream_t s) {
+  for (int k0 = 0; k0 < count; k0 += kCopySet) {
+    CopySet set{};
+    set.n = std::min(kCopySet, count - k0);
+    uint64_t blocks = 0;
+    for (int k = 0; k < set.n; ++k) {
+      set.dst[k] = static_cast<char*>(dst[k0 + k]);
+      set.src[k] = static_cast<const char*>(src[k0 + k]);
+      set.bytes[k] = bytes[k0 + k];
+      set.first[k] = (uint32_t)blocks;
+      blocks += (bytes[k0 + k] + kCopyBlock - 1) / kCopyBlock;
+      if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    }
+    set.first[set.n] = (uint32_t)blocks;
+    hipLaunchKernelGGL(copy_kernel, dim3((unsigned)blocks), dim3(TPB), 0, s, set);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 hipError_t accumulate(float* a, const float* b, int64_t n, hipStream_t s) {
   const bool vec = aligned16(a) && aligned16(b);
   hipLaunchKernelGGL(acc_kernel, dim3(grid_for((n + 3) / 4)), dim3(TPB), 0, s, a, b, n, vec);

@@ -547,3 +547,31 @@ def test_attention(B, T, H, dh, causal):
     assert np.array_equal(out[1], P)
     rd = ops.attention_bwd(qkv.astype(np.float64), rP, G.astype(np.float64), B, T, H)
     assert rel_err(out[3], rd) < TOL
+
+
+@pytest.mark.parametrize("layout", ["pool", "bestfit"])
+def test_upload_download_sizes(layout):
+    """In-core upload and download of more variables than one launch takes, sizes around 16 bytes
+    and a workgroup's 16 KiB among them: every byte arrives, and nothing else changes."""
+    sizes = [1, 3, 15, 16, 17, 31, 4095, 4096, 16383, 16384, 16385, 32768, 49157, 300001] * 5
+    ctx = ooc.Context(0)
+    try:
+        ids = [ctx.add_var(n, ooc.STATE) for n in sizes]
+        for v in ids:
+            ctx.add_fn("noop", [v], [ooc.R], [])
+        ctx.set_chunk(4096)
+        ctx.set_layout(layout)
+        ctx.build_schedule()
+        ctx.prepare()
+        data = [rng.integers(0, 256, n, dtype=np.uint8) for n in sizes]
+        for v, a in zip(ids, data):
+            ctx.host_view(v, np.uint8)[...] = a
+        ctx.upload()
+        ctx.step(0.0, 0.0)
+        for v in ids:
+            ctx.host_view(v, np.uint8)[...] = 7
+        ctx.download()
+        for v, a in zip(ids, data):
+            assert np.array_equal(ctx.host_view(v, np.uint8), a)
+    finally:
+        ctx.close()
