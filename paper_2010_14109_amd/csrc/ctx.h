@@ -44,6 +44,8 @@ struct FnProgram {
   std::vector<int32_t> cwaits;  // compute stream waits before f_i's kernels
   std::vector<void*> ptrs;      // device address of each of f_i's variables
   std::vector<uint64_t> sizes;  // and its size in bytes
+  std::vector<uint8_t> dead;    // nothing reads what f_i leaves in it: a TEMP that f_i writes and
+                                // whose next function, if any, only writes it
   std::vector<Copy> d2h;        // swap-outs issued in f_i's POST phase
   int32_t ev_pre, ev_fn;        // compute stream, around f_i's kernels
 };

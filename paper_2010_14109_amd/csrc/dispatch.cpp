@@ -6,8 +6,8 @@
 
 namespace ooc {
 
-hipError_t launch_fn(const Fn& fn, void* const* p, const uint64_t* bytes, float lr, float mu,
-                     hipStream_t s) {
+hipError_t launch_fn(const Fn& fn, void* const* p, const uint64_t* bytes, const uint8_t* dead,
+                     float lr, float mu, hipStream_t s) {
   const auto& a = fn.attrs;
   auto F = [&](int j) { return static_cast<float*>(p[j]); };
   auto conv = [&]() {
@@ -94,9 +94,10 @@ hipError_t launch_fn(const Fn& fn, void* const* p, const uint64_t* bytes, float 
     case OOC_OP_GELU_BWD:
       return gelu_bwd(F(0), F(1), F(2), a[0], s);
     case OOC_OP_ATTENTION_FWD:
-      return attention_fwd(F(0), F(1), F(2), a[0], a[1], a[2], a[3], a[4] != 0, s);
+      return attention_fwd(F(0), F(1), F(2), a[0], a[1], a[2], a[3], a[4] != 0, !dead[1], s);
     case OOC_OP_ATTENTION_BWD:
-      return attention_bwd(F(0), F(1), F(2), F(3), F(4), a[0], a[1], a[2], a[3], a[4] != 0, s);
+      return attention_bwd(F(0), F(1), F(2), F(3), F(4), a[0], a[1], a[2], a[3], a[4] != 0, !dead[1],
+                           !dead[4], s);
     case OOC_OP_CONCAT_FWD: {
       const int k = (int)fn.vars.size() - 1;
       return concat(true, F(k), p, a.data() + 1, k, a[0], s);

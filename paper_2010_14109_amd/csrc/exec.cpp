@@ -127,6 +127,16 @@ static ooc_status compile(ooc_ctx* ctx) {
   }
   ctx->ev_end = new_event(ctx, 0);
 
+  {
+    std::vector<uint8_t> read_next(nv, 0);   // the next function that uses the variable reads it
+    for (int64_t i = N - 1; i >= 0; --i) {
+      for (const auto& u : ctx->fns[i].vars)
+        ctx->prog[i].dead.push_back(ctx->vars[u.var].kind == OOC_TEMP && (u.access & OOC_W) &&
+                                    !read_next[u.var]);
+      for (const auto& u : ctx->fns[i].vars) read_next[u.var] = (u.access & OOC_R) != 0;
+    }
+  }
+
   // swap-outs that a later CANCEL undoes
   std::vector<uint8_t> cancelled(ops.size(), 0);
   {
@@ -930,7 +940,8 @@ ooc_status step(ooc_ctx* ctx, float lr, float mu, float* loss_out) {
     if (!issued_by_stager(fp.cwaits)) return OOC_E_DEVICE;
     for (int32_t w : fp.cwaits) HIPCK(hipStreamWaitEvent(cs, ctx->events[w], 0));
     HIPCK(hipEventRecord(ctx->events[fp.ev_pre], cs));
-    hipError_t e = launch_fn(ctx->fns[i], fp.ptrs.data(), fp.sizes.data(), lr, mu, cs);
+    hipError_t e = launch_fn(ctx->fns[i], fp.ptrs.data(), fp.sizes.data(), fp.dead.data(), lr, mu,
+                             cs);
     if (e != hipSuccess) {
       ctx->err = "kernel launch of function " + std::to_string(i) + " failed: " +
                  hipGetErrorString(e);

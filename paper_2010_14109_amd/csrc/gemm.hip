@@ -706,12 +706,12 @@ __device__ inline float4 read_op(const float* lds, int i, int k) {
 }
 
 // Batched problems (grid z): batch z = (zo, zi) with zi = z mod inner; operand
-// and result pointers move by zo * outer stride + zi * inner stride.  With
-// skip_upper, tiles strictly above the diagonal return without writing.
+// and result pointers move by zo * outer stride + zi * inner stride.  causal:
+// see BatchStrides.
 struct Batch {
   int64_t inner;
   int64_t a_o, a_i, b_o, b_i, c_o, c_i;
-  int64_t skip_upper;
+  int64_t causal;
 };
 
 template <class L>
@@ -875,11 +875,14 @@ __global__ __launch_bounds__(THREADS, (WaveGrid<BM, BN>::kWaves)) void gemm_kern
   const int tm = first_m + (t % per_group) % gsize;
   const int tn = (t % per_group) / gsize;
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+  int64_t kb = slice * k_slice;
+  int64_t ke = min(K, kb + k_slice);
   if constexpr (BATCHED) {
-    if (bt.skip_upper && n0 >= m0 + BM) return;   // the whole workgroup leaves together
+    // the whole workgroup leaves together
+    if (bt.causal == BatchStrides::kUpperC && n0 >= m0 + BM) return;
+    if (bt.causal == BatchStrides::kLowerA) ke = min(ke, m0 + BM);
+    if (bt.causal == BatchStrides::kLowerAT) kb = max(kb, m0);
   }
-  const int64_t kb = slice * k_slice;
-  const int64_t ke = min(K, kb + k_slice);
 
   la.init(m0, M);
   lb.init(n0, N);
@@ -1275,7 +1278,7 @@ hipError_t gemm_batched(bool a_rowk, const float* A, int64_t lda, bool b_rowk, c
                         int64_t ldb, float* C, int64_t ldc, int64_t M, int64_t N, int64_t K,
                         int64_t batches, const BatchStrides& st, hipStream_t s) {
   const Batch bt{st.inner,   st.a_outer, st.a_inner, st.b_outer,
-                 st.b_inner, st.c_outer, st.c_inner, st.skip_upper};
+                 st.b_inner, st.c_outer, st.c_inner, st.causal};
   const auto fa = dense(A, lda, K), fb = dense(B, ldb, K);
 #define GEMM_BATCHED_CASE(LA, LB) \
   return dispatch_dense<LA, LB, false, true>(fa, fb, C, ldc, nullptr, M, N, K, 1, s, batches, bt)

@@ -8,9 +8,9 @@
 namespace ooc {
 
 // Runs function fn on stream s; ptrs[j] is the device address of fn.vars[j],
-// bytes[j] its size.
-hipError_t launch_fn(const Fn& fn, void* const* ptrs, const uint64_t* bytes, float lr, float mu,
-                     hipStream_t s);
+// bytes[j] its size; dead[j]: nothing reads what fn leaves in it.
+hipError_t launch_fn(const Fn& fn, void* const* ptrs, const uint64_t* bytes, const uint8_t* dead,
+                     float lr, float mu, hipStream_t s);
 
 // GEMM family (gemm.hip).  Shapes as in the operation table of ooc.h.
 hipError_t linear_fwd(const float* X, const float* W, const float* b, float* Y, int64_t M,
@@ -26,8 +26,11 @@ hipError_t linear_bwd_x(const float* W, const float* dY, float* dX, int64_t M, i
 struct BatchStrides {
   int64_t inner;
   int64_t a_outer, a_inner, b_outer, b_inner, c_outer, c_inner;
-  // nonzero: C tiles whose every entry lies above the diagonal (column > row) are left unwritten
-  int64_t skip_upper = 0;
+  // kUpperC: C tiles whose every entry lies above the diagonal (column > row) are left unwritten.
+  // kLowerA / kLowerAT: A[m][k] is zero, or not read, where k > m / k < m, as far as the 128-wide
+  // tile of the diagonal reaches (in which it holds zeros)
+  enum Causal { kFull = 0, kUpperC, kLowerA, kLowerAT };
+  int64_t causal = kFull;
 };
 hipError_t gemm_batched(bool a_rowk, const float* A, int64_t lda, bool b_rowk, const float* B,
                         int64_t ldb, float* C, int64_t ldc, int64_t M, int64_t N, int64_t K,
@@ -94,10 +97,12 @@ hipError_t layernorm_bwd(const float* x, const float* gamma, float* stats, const
                          int64_t slices, hipStream_t s);
 hipError_t gelu_fwd(const float* x, float* y, int64_t n, hipStream_t s);
 hipError_t gelu_bwd(const float* x, const float* dy, float* dx, int64_t n, hipStream_t s);
+// whole_P, whole_dS: also the masked entries that nothing in here reads are written (as zeros)
 hipError_t attention_fwd(const float* qkv, float* P, float* y, int64_t B, int64_t T, int64_t H,
-                         int64_t dh, bool causal, hipStream_t s);
+                         int64_t dh, bool causal, bool whole_P, hipStream_t s);
 hipError_t attention_bwd(const float* qkv, float* P, const float* dy, float* dqkv, float* dS,
-                         int64_t B, int64_t T, int64_t H, int64_t dh, bool causal, hipStream_t s);
+                         int64_t B, int64_t T, int64_t H, int64_t dh, bool causal, bool whole_P,
+                         bool whole_dS, hipStream_t s);
 
 hipError_t mix(void* const* ptrs, const uint64_t* words, int nvars, uint32_t seed, hipStream_t s,
                bool y_read);

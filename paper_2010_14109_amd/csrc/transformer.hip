@@ -15,7 +15,10 @@
 // batched MFMA GEMMs compute q k^T into P and P v into the context, a row
 // kernel applies the scale, the causal mask and the softmax in place.  The
 // backward pass runs the four batched GEMMs of dv, dP, dq, dk around the row
-// kernel dS = scale P (dP - rowsum(dP P)).
+// kernel dS = scale P (dP - rowsum(dP P)).  These passes are bound by the
+// traffic of the T x T matrices.  Under the causal mask the products neither
+// compute nor read past the diagonal's tile, and the row kernels write zeros
+// past it only where something outside the function can read them.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -386,9 +389,15 @@ __global__ void gelu4_kernel(const float4* __restrict__ x, const float4* __restr
 }
 
 // ---------------------------------------------------------------- attention rows
+// Columns a row kernel writes of a row whose first n columns are not masked: all T, or up to the
+// end of the diagonal's 128-wide tile, past which the products of this layer read nothing.
+__device__ inline int64_t written(int64_t n, int64_t T, bool whole) {
+  return whole ? T : min(T, (n + 127) / 128 * 128);
+}
+
 // P row (b, h, i) in place: scale, causal mask (keys j > i get 0), softmax
 __global__ void attn_softmax(float* __restrict__ P, int64_t nrows, int64_t T, float scale,
-                             bool causal) {
+                             bool causal, bool whole) {
   const int64_t row = (int64_t)blockIdx.x * (TPB / 64) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (row >= nrows) return;
@@ -402,7 +411,8 @@ __global__ void attn_softmax(float* __restrict__ P, int64_t nrows, int64_t T, fl
   for (int64_t j = lane; j < n; j += 64) sum += expf(p[j] * scale - mx);
   sum = wave_sum(sum);
   const float inv = 1.f / sum;
-  for (int64_t j = lane; j < T; j += 64) p[j] = j < n ? expf(p[j] * scale - mx) * inv : 0.f;
+  const int64_t end = written(n, T, whole);
+  for (int64_t j = lane; j < end; j += 64) p[j] = j < n ? expf(p[j] * scale - mx) * inv : 0.f;
 }
 
 // The same two row operations with the row held in registers: lane l owns the float4s
@@ -410,7 +420,7 @@ __global__ void attn_softmax(float* __restrict__ P, int64_t nrows, int64_t T, fl
 // mask, keys j >= n are not read: their P is 0, and so is their dS.
 template <int K>
 __global__ void attn_softmax_regs(float* __restrict__ P, int64_t nrows, int64_t T, float scale,
-                                  bool causal) {
+                                  bool causal, bool whole) {
   const int64_t row = (int64_t)blockIdx.x * (TPB / 64) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (row >= nrows) return;
@@ -441,15 +451,16 @@ __global__ void attn_softmax_regs(float* __restrict__ P, int64_t nrows, int64_t 
   }
   sum = wave_sum(sum);
   const float inv = 1.f / sum;
+  const int64_t end = written(n, T, whole);
 #pragma unroll
   for (int k = 0; k < K; ++k)
-    if (4 * (lane + 64 * k) < T)
+    if (4 * (lane + 64 * k) < end)
       p[lane + 64 * k] = make_float4(v[k][0] * inv, v[k][1] * inv, v[k][2] * inv, v[k][3] * inv);
 }
 
 template <int K>
 __global__ void attn_softmax_bwd_regs(const float* __restrict__ P, float* __restrict__ dS,
-                                      int64_t nrows, int64_t T, float scale, bool causal) {
+                                      int64_t nrows, int64_t T, float scale, bool causal, bool whole) {
   const int64_t row = (int64_t)blockIdx.x * (TPB / 64) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (row >= nrows) return;
@@ -468,9 +479,10 @@ __global__ void attn_softmax_bwd_regs(const float* __restrict__ P, float* __rest
     dot += gv[k].x * pv[k].x + gv[k].y * pv[k].y + gv[k].z * pv[k].z + gv[k].w * pv[k].w;
   }
   dot = wave_sum(dot);
+  const int64_t end = written(n, T, whole);
 #pragma unroll
   for (int k = 0; k < K; ++k)
-    if (4 * (lane + 64 * k) < T)
+    if (4 * (lane + 64 * k) < end)
       g[lane + 64 * k] = make_float4(scale * pv[k].x * (gv[k].x - dot),
                                      scale * pv[k].y * (gv[k].y - dot),
                                      scale * pv[k].z * (gv[k].z - dot),
@@ -480,7 +492,7 @@ __global__ void attn_softmax_bwd_regs(const float* __restrict__ P, float* __rest
 // dS row in place: dS = scale P (dP - sum_j dP P).  Under the causal mask the keys
 // j >= n are neither read (dP there may be unwritten) nor kept: their dS is 0.
 __global__ void attn_softmax_bwd(const float* __restrict__ P, float* __restrict__ dS,
-                                 int64_t nrows, int64_t T, float scale, bool causal) {
+                                 int64_t nrows, int64_t T, float scale, bool causal, bool whole) {
   const int64_t row = (int64_t)blockIdx.x * (TPB / 64) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (row >= nrows) return;
@@ -490,7 +502,8 @@ __global__ void attn_softmax_bwd(const float* __restrict__ P, float* __restrict_
   float dot = 0.f;
   for (int64_t j = lane; j < n; j += 64) dot += g[j] * p[j];
   dot = wave_sum(dot);
-  for (int64_t j = lane; j < T; j += 64) g[j] = j < n ? scale * p[j] * (g[j] - dot) : 0.f;
+  const int64_t end = written(n, T, whole);
+  for (int64_t j = lane; j < end; j += 64) g[j] = j < n ? scale * p[j] * (g[j] - dot) : 0.f;
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -506,32 +519,34 @@ hipError_t gelu_launch(const float* x, const float* dy, float* out, int64_t n, b
   return hipGetLastError();
 }
 
-// rows of T floats: the register kernels need T % 4 == 0, T <= 1024 and an aligned base
+// rows of T floats: the register kernels need T % 4 == 0, T <= 2048 and an aligned base
 int softmax_regs(const float* base, int64_t T) {
-  if (T % 4 != 0 || T > 1024 || !aligned16(base)) return 0;
-  return T <= 256 ? 1 : T <= 512 ? 2 : 4;
+  if (T % 4 != 0 || T > 2048 || !aligned16(base)) return 0;
+  return T <= 256 ? 1 : T <= 512 ? 2 : T <= 1024 ? 4 : 8;
 }
 
-hipError_t softmax_rows(float* P, int64_t nrows, int64_t T, float scale, bool causal,
+hipError_t softmax_rows(float* P, int64_t nrows, int64_t T, float scale, bool causal, bool whole,
                         hipStream_t s) {
   const dim3 grid((unsigned)((nrows + 3) / 4));
   switch (softmax_regs(P, T)) {
-    case 1: hipLaunchKernelGGL(attn_softmax_regs<1>, grid, dim3(TPB), 0, s, P, nrows, T, scale, causal); break;
-    case 2: hipLaunchKernelGGL(attn_softmax_regs<2>, grid, dim3(TPB), 0, s, P, nrows, T, scale, causal); break;
-    case 4: hipLaunchKernelGGL(attn_softmax_regs<4>, grid, dim3(TPB), 0, s, P, nrows, T, scale, causal); break;
-    default: hipLaunchKernelGGL(attn_softmax, grid, dim3(TPB), 0, s, P, nrows, T, scale, causal);
+    case 1: hipLaunchKernelGGL(attn_softmax_regs<1>, grid, dim3(TPB), 0, s, P, nrows, T, scale, causal, whole); break;
+    case 2: hipLaunchKernelGGL(attn_softmax_regs<2>, grid, dim3(TPB), 0, s, P, nrows, T, scale, causal, whole); break;
+    case 4: hipLaunchKernelGGL(attn_softmax_regs<4>, grid, dim3(TPB), 0, s, P, nrows, T, scale, causal, whole); break;
+    case 8: hipLaunchKernelGGL(attn_softmax_regs<8>, grid, dim3(TPB), 0, s, P, nrows, T, scale, causal, whole); break;
+    default: hipLaunchKernelGGL(attn_softmax, grid, dim3(TPB), 0, s, P, nrows, T, scale, causal, whole);
   }
   return hipGetLastError();
 }
 
 hipError_t softmax_rows_bwd(const float* P, float* dS, int64_t nrows, int64_t T, float scale,
-                            bool causal, hipStream_t s) {
+                            bool causal, bool whole, hipStream_t s) {
   const dim3 grid((unsigned)((nrows + 3) / 4));
   switch (aligned16(dS) ? softmax_regs(P, T) : 0) {
-    case 1: hipLaunchKernelGGL(attn_softmax_bwd_regs<1>, grid, dim3(TPB), 0, s, P, dS, nrows, T, scale, causal); break;
-    case 2: hipLaunchKernelGGL(attn_softmax_bwd_regs<2>, grid, dim3(TPB), 0, s, P, dS, nrows, T, scale, causal); break;
-    case 4: hipLaunchKernelGGL(attn_softmax_bwd_regs<4>, grid, dim3(TPB), 0, s, P, dS, nrows, T, scale, causal); break;
-    default: hipLaunchKernelGGL(attn_softmax_bwd, grid, dim3(TPB), 0, s, P, dS, nrows, T, scale, causal);
+    case 1: hipLaunchKernelGGL(attn_softmax_bwd_regs<1>, grid, dim3(TPB), 0, s, P, dS, nrows, T, scale, causal, whole); break;
+    case 2: hipLaunchKernelGGL(attn_softmax_bwd_regs<2>, grid, dim3(TPB), 0, s, P, dS, nrows, T, scale, causal, whole); break;
+    case 4: hipLaunchKernelGGL(attn_softmax_bwd_regs<4>, grid, dim3(TPB), 0, s, P, dS, nrows, T, scale, causal, whole); break;
+    case 8: hipLaunchKernelGGL(attn_softmax_bwd_regs<8>, grid, dim3(TPB), 0, s, P, dS, nrows, T, scale, causal, whole); break;
+    default: hipLaunchKernelGGL(attn_softmax_bwd, grid, dim3(TPB), 0, s, P, dS, nrows, T, scale, causal, whole);
   }
   return hipGetLastError();
 }
@@ -668,23 +683,25 @@ hipError_t gelu_bwd(const float* x, const float* dy, float* dx, int64_t n, hipSt
 
 // P = softmax(q k^T / sqrt(dh)) per batch and head, masked when causal
 static hipError_t attention_probs(const float* qkv, float* P, int64_t B, int64_t T, int64_t H,
-                                  int64_t dh, bool causal, hipStream_t s) {
+                                  int64_t dh, bool causal, bool whole, hipStream_t s) {
   const int64_t d = H * dh, d3 = 3 * d, TT = T * T;
   // S = q k^T into P; under the causal mask the tiles above the diagonal are left to the
-  // softmax, which writes them as 0 without reading them
-  BatchStrides st{H, T * d3, dh, T * d3, dh, H * TT, TT, causal ? 1 : 0};
+  // softmax, which does not read them
+  BatchStrides st{H, T * d3, dh, T * d3, dh, H * TT, TT,
+                  causal ? BatchStrides::kUpperC : BatchStrides::kFull};
   hipError_t e = gemm_batched(true, qkv, d3, true, qkv + d, d3, P, T, T, T, dh, B * H, st, s);
   if (e != hipSuccess) return e;
-  return softmax_rows(P, B * H * T, T, 1.f / sqrtf((float)dh), causal, s);
+  return softmax_rows(P, B * H * T, T, 1.f / sqrtf((float)dh), causal, whole, s);
 }
 
 hipError_t attention_fwd(const float* qkv, float* P, float* y, int64_t B, int64_t T, int64_t H,
-                         int64_t dh, bool causal, hipStream_t s) {
+                         int64_t dh, bool causal, bool whole_P, hipStream_t s) {
   const int64_t d = H * dh, d3 = 3 * d, TT = T * T;
-  hipError_t e = attention_probs(qkv, P, B, T, H, dh, causal, s);
+  hipError_t e = attention_probs(qkv, P, B, T, H, dh, causal, whole_P, s);
   if (e != hipSuccess) return e;
   // context = P v
-  BatchStrides sv{H, H * TT, TT, T * d3, dh, T * d, dh};
+  BatchStrides sv{H, H * TT, TT, T * d3, dh, T * d, dh,
+                  causal ? BatchStrides::kLowerA : BatchStrides::kFull};
   return gemm_batched(true, P, T, false, qkv + 2 * d, d3, y, d, T, dh, T, B * H, sv, s);
 }
 
@@ -694,29 +711,34 @@ hipError_t attention_fwd(const float* qkv, float* P, float* y, int64_t B, int64_
 // q k^T product and one softmax pass.  The same kernels on the same q, k give the forward's
 // P bit for bit.
 hipError_t attention_bwd(const float* qkv, float* P, const float* dy, float* dqkv, float* dS,
-                         int64_t B, int64_t T, int64_t H, int64_t dh, bool causal, hipStream_t s) {
+                         int64_t B, int64_t T, int64_t H, int64_t dh, bool causal, bool whole_P,
+                         bool whole_dS, hipStream_t s) {
   const int64_t d = H * dh, d3 = 3 * d, TT = T * T;
-  hipError_t e = attention_probs(qkv, P, B, T, H, dh, causal, s);
+  const int64_t lower = causal ? BatchStrides::kLowerA : BatchStrides::kFull;
+  const int64_t lower_t = causal ? BatchStrides::kLowerAT : BatchStrides::kFull;
+  hipError_t e = attention_probs(qkv, P, B, T, H, dh, causal, whole_P, s);
   if (e != hipSuccess) return e;
   // dv = P^T dO
-  BatchStrides s1{H, H * TT, TT, T * d, dh, T * d3, dh};
+  BatchStrides s1{H, H * TT, TT, T * d, dh, T * d3, dh, lower_t};
   if ((e = gemm_batched(false, P, T, false, dy, d, dqkv + 2 * d, d3, T, dh, T, B * H, s1, s)) !=
       hipSuccess)
     return e;
   // dP = dO v^T into dS (tiles above the diagonal likewise left to the softmax backward)
-  BatchStrides s2{H, T * d, dh, T * d3, dh, H * TT, TT, causal ? 1 : 0};
+  BatchStrides s2{H, T * d, dh, T * d3, dh, H * TT, TT,
+                  causal ? BatchStrides::kUpperC : BatchStrides::kFull};
   if ((e = gemm_batched(true, dy, d, true, qkv + 2 * d, d3, dS, T, T, T, dh, B * H, s2, s)) !=
       hipSuccess)
     return e;
-  if ((e = softmax_rows_bwd(P, dS, B * H * T, T, 1.f / sqrtf((float)dh), causal, s)) !=
+  if ((e = softmax_rows_bwd(P, dS, B * H * T, T, 1.f / sqrtf((float)dh), causal, whole_dS, s)) !=
       hipSuccess)
     return e;
   // dq = dS k
-  BatchStrides s3{H, H * TT, TT, T * d3, dh, T * d3, dh};
+  BatchStrides s3{H, H * TT, TT, T * d3, dh, T * d3, dh, lower};
   if ((e = gemm_batched(true, dS, T, false, qkv + d, d3, dqkv, d3, T, dh, T, B * H, s3, s)) !=
       hipSuccess)
     return e;
   // dk = dS^T q
+  s3.causal = lower_t;
   return gemm_batched(false, dS, T, false, qkv, d3, dqkv + d, d3, T, dh, T, B * H, s3, s);
 }
 

@@ -575,3 +575,43 @@ def test_upload_download_sizes(layout):
             assert np.array_equal(ctx.host_view(v, np.uint8), a)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("B,T,H,dh,causal", [(2, 5, 2, 8, 1), (1, 128, 2, 16, 1), (2, 130, 1, 20, 1),
+                                             (1, 300, 2, 64, 1), (1, 1030, 1, 9, 1), (1, 1028, 1, 8, 1),
+                                             (1, 132, 2, 12, 0)])
+def test_attention_scratch(B, T, H, dh, causal):
+    """P and dS as TEMP variables, whose masked parts nothing can read, give the same bits as P and
+    dS kept as outputs (checked whole against the oracle elsewhere), also where the memory they
+    use holds NaN before."""
+    d = H * dh
+    qkv, dy = f32(B * T, 3 * d), f32(B * T, d)
+    attrs = [B, T, H, dh, causal]
+    nan = np.full(B * H * T * T, np.nan, np.float32)
+
+    def run(kind):
+        ctx = ooc.Context(0)
+        try:
+            q, g = ctx.add_var(qkv.nbytes, ooc.INPUT), ctx.add_var(dy.nbytes, ooc.INPUT)
+            fill = ctx.add_var(nan.nbytes, ooc.INPUT)
+            y, dq = ctx.add_var(dy.nbytes, ooc.OUTPUT), ctx.add_var(qkv.nbytes, ooc.OUTPUT)
+            P, Pb, dS = (ctx.add_var(nan.nbytes, kind) for _ in range(3))
+            for v in (P, Pb, dS):   # the same memory holds NaN first
+                ctx.add_fn("concat_fwd", [fill, v], [ooc.R, ooc.W], [1, nan.size])
+            ctx.add_fn("attention_fwd", [q, P, y], [ooc.R, ooc.W, ooc.W], attrs)
+            ctx.add_fn("attention_bwd", [q, Pb, g, dq, dS], [ooc.R, ooc.W, ooc.R, ooc.W, ooc.W],
+                       attrs)
+            ctx.set_chunk(4096)
+            ctx.build_schedule()
+            ctx.prepare()
+            for v, a in ((q, qkv), (g, dy), (fill, nan)):
+                ctx.host_view(v)[...] = a.reshape(-1)
+            ctx.upload()
+            ctx.step(0.0, 0.0)
+            ctx.download()
+            return np.array(ctx.host_view(y)), np.array(ctx.host_view(dq))
+        finally:
+            ctx.close()
+
+    for a, b in zip(run(ooc.TEMP), run(ooc.OUTPUT)):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
