@@ -469,7 +469,9 @@ ooc_status ooc_wgrad_slices(int32_t op, const int64_t *attrs, int32_t n_attrs, i
 
 /* Duration in milliseconds of each function's kernels in the last step,
  * measured with events on the compute stream right before and after its
- * launches (waits for swap-ins excluded).  buf caller-owned (cap entries);
+ * launches (waits for swap-ins excluded).  In core, a batch normalisation and
+ * the ReLU right behind it may run as one, in the ReLU's place (forward) or
+ * with the normalisation's sums taken there (backward).  buf caller-owned (cap entries);
  * *n receives the function count.  OOC_E_STATE before the first step. */
 ooc_status ooc_fn_times(const ooc_ctx *ctx, double *buf, uint64_t cap, uint64_t *n);
 

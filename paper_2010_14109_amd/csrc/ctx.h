@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "kernels.h"
 
 namespace ooc {
 
@@ -46,6 +47,8 @@ struct FnProgram {
   std::vector<uint64_t> sizes;  // and its size in bytes
   std::vector<uint8_t> dead;    // nothing reads what f_i leaves in it: a TEMP that f_i writes and
                                 // whose next function, if any, only writes it
+  Join join = Join::kNone;      // in core: kernels shared with a neighbour
+  BnBehind bn{};                // and the batch normalisation that a ReLU's launch covers
   std::vector<Copy> d2h;        // swap-outs issued in f_i's POST phase
   int32_t ev_pre, ev_fn;        // compute stream, around f_i's kernels
 };

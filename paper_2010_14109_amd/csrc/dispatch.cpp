@@ -7,7 +7,7 @@
 namespace ooc {
 
 hipError_t launch_fn(const Fn& fn, void* const* p, const uint64_t* bytes, const uint8_t* dead,
-                     float lr, float mu, hipStream_t s) {
+                     Join join, const BnBehind& bn, float lr, float mu, hipStream_t s) {
   const auto& a = fn.attrs;
   auto F = [&](int j) { return static_cast<float*>(p[j]); };
   auto conv = [&]() {
@@ -25,8 +25,11 @@ hipError_t launch_fn(const Fn& fn, void* const* p, const uint64_t* bytes, const 
     case OOC_OP_LINEAR_BWD_X:
       return linear_bwd_x(F(0), F(1), F(2), a[0], a[1], a[2], s);
     case OOC_OP_RELU_FWD:
+      if (join == Join::kReluOfBn)
+        return bn_fwd(bn.x, bn.gamma, bn.beta, F(1), bn.stats, bn.rows, bn.C, bn.slices, true, s);
       return relu_fwd(F(0), F(1), a[0], s);
     case OOC_OP_RELU_BWD:
+      if (join == Join::kReluBwdSums) return relu_bn_bwd_sums(bn, F(1), F(2), s);
       return relu_bwd(F(0), F(1), F(2), a[0], s);
     case OOC_OP_ADD:
       return add(F(0), F(1), F(2), a[0], s);
@@ -68,8 +71,13 @@ hipError_t launch_fn(const Fn& fn, void* const* p, const uint64_t* bytes, const 
     case OOC_OP_CONV_BWD_W:
       return conv_bwd_w(F(0), F(1), F(2), a[11] > 1 ? F(3) : nullptr, a[11], conv(), s);
     case OOC_OP_BN_FWD:
-      return bn_fwd(F(0), F(1), F(2), F(3), F(4), a[0], a[1], a[2], s);
+      if (join == Join::kBnBeforeRelu) return hipSuccess;
+      return bn_fwd(F(0), F(1), F(2), F(3), F(4), a[0], a[1], a[2], false, s);
     case OOC_OP_BN_BWD:
+      if (join != Join::kBnSumsDone) {
+        const hipError_t e = bn_bwd_sums(F(0), F(2), F(3), a[0], a[1], a[2], s);
+        if (e != hipSuccess) return e;
+      }
       return bn_bwd(F(0), F(1), F(2), F(3), F(4), F(5), F(6), a[0], a[1], a[2], s);
     case OOC_OP_MAXPOOL_FWD:
       return maxpool_fwd(F(0), F(1), static_cast<uint8_t*>(p[2]), pool(), s);

@@ -244,7 +244,7 @@ static ooc_status compile(ooc_ctx* ctx) {
           add_waits(&fp.cwaits, preds[J], 0);
         acquired[J] = 1;
       }
-      fp.ptrs.push_back(ctx->iv_ptr[J]);
+      fp.ptrs.push_back(ctx->iv_ptr[J]);   // in core the same at every use (see plan_joins)
       fp.sizes.push_back(ctx->vars[fv.var].bytes);
       last_fn[J] = i;
       if (fv.access & OOC_W) host_valid[fv.var] = 0;
@@ -271,6 +271,20 @@ static ooc_status compile(ooc_ctx* ctx) {
         closed(J);
       }
       ++k;
+    }
+  }
+  if (ctx->incore) {
+    JoinPlan joins;
+    plan_joins(ctx->vars, ctx->fns, &joins);
+    for (int64_t i = 0; i < N; ++i) {
+      FnProgram& fp = ctx->prog[i];
+      fp.join = joins.join[i];
+      const int64_t b = joins.bn_fwd[i];
+      if (b < 0) continue;
+      void* const* p = ctx->prog[b].ptrs.data();   // X, gamma, beta, Y, stats
+      const auto& a = ctx->fns[fp.join == Join::kReluBwdSums ? i + 1 : b].attrs;
+      fp.bn = BnBehind{static_cast<float*>(p[0]), static_cast<float*>(p[1]),
+                       static_cast<float*>(p[2]), static_cast<float*>(p[4]), a[0], a[1], a[2]};
     }
   }
   return OOC_OK;
@@ -940,8 +954,8 @@ ooc_status step(ooc_ctx* ctx, float lr, float mu, float* loss_out) {
     if (!issued_by_stager(fp.cwaits)) return OOC_E_DEVICE;
     for (int32_t w : fp.cwaits) HIPCK(hipStreamWaitEvent(cs, ctx->events[w], 0));
     HIPCK(hipEventRecord(ctx->events[fp.ev_pre], cs));
-    hipError_t e = launch_fn(ctx->fns[i], fp.ptrs.data(), fp.sizes.data(), fp.dead.data(), lr, mu,
-                             cs);
+    hipError_t e = launch_fn(ctx->fns[i], fp.ptrs.data(), fp.sizes.data(), fp.dead.data(), fp.join,
+                             fp.bn, lr, mu, cs);
     if (e != hipSuccess) {
       ctx->err = "kernel launch of function " + std::to_string(i) + " failed: " +
                  hipGetErrorString(e);

@@ -27,6 +27,19 @@ struct Fn {
   std::vector<int64_t> attrs;
 };
 
+// How a function's kernels join those of its neighbour (in core only; see plan_joins).
+enum class Join : uint8_t {
+  kNone,
+  kBnBeforeRelu,   // BN_FWD: launches nothing, the ReLU behind it does all
+  kReluOfBn,       // RELU_FWD: batch normalisation and ReLU in one
+  kReluBwdSums,    // RELU_BWD: also takes the sums that the BN_BWD behind it starts from
+  kBnSumsDone,     // that BN_BWD
+};
+struct JoinPlan {
+  std::vector<Join> join;       // per function
+  std::vector<int64_t> bn_fwd;  // of a kReluOfBn or kReluBwdSums: its BN_FWD, else -1
+};
+
 struct Op {
   int32_t fn;
   uint8_t phase;
@@ -78,6 +91,7 @@ ooc_status build_schedule(const std::vector<Var>& vars, const std::vector<Fn>& f
                           int64_t threshold = -1, int wait_order = OOC_WAIT_OLDEST);
 // In-core plan: persistent variables resident for the whole step, TEMPs from
 // first to last use, no transfers.
+void plan_joins(const std::vector<Var>& vars, const std::vector<Fn>& fns, JoinPlan* out);
 void build_incore(const std::vector<Var>& vars, const std::vector<Fn>& fns, uint64_t chunk,
                   Schedule* out);
 uint64_t incore_peak(const std::vector<Var>& vars, const std::vector<Fn>& fns, uint64_t chunk);

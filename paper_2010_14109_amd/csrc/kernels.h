@@ -7,10 +7,17 @@
 
 namespace ooc {
 
+// Addresses and sizes of a batch normalisation whose work joins that of the ReLU behind it.
+struct BnBehind {
+  const float *x, *gamma, *beta;
+  float* stats;
+  int64_t rows, C, slices;
+};
+
 // Runs function fn on stream s; ptrs[j] is the device address of fn.vars[j],
-// bytes[j] its size; dead[j]: nothing reads what fn leaves in it.
+// bytes[j] its size; dead[j]: nothing reads what fn leaves in it.  join, bn: see Join.
 hipError_t launch_fn(const Fn& fn, void* const* ptrs, const uint64_t* bytes, const uint8_t* dead,
-                     float lr, float mu, hipStream_t s);
+                     Join join, const BnBehind& bn, float lr, float mu, hipStream_t s);
 
 // GEMM family (gemm.hip).  Shapes as in the operation table of ooc.h.
 hipError_t linear_fwd(const float* X, const float* W, const float* b, float* Y, int64_t M,
@@ -64,8 +71,14 @@ hipError_t copy_many(int count, void* const* dst, const void* const* src, const 
                      hipStream_t s);
 hipError_t softmax_ce(const float* logits, const int32_t* labels, float* loss, float* dlogits,
                       int64_t N, int64_t classes, hipStream_t s);
+// relu: y is the ReLU of the normalised values
 hipError_t bn_fwd(const float* x, const float* gamma, const float* beta, float* y, float* stats,
-                  int64_t rows, int64_t C, int64_t slices, hipStream_t s);
+                  int64_t rows, int64_t C, int64_t slices, bool relu, hipStream_t s);
+// The slice sums that bn_bwd starts from, into stats; the second one behind a ReLU whose output
+// gradient is dy, writing the ReLU's input gradient dr too.
+hipError_t bn_bwd_sums(const float* x, float* stats, const float* dy, int64_t rows, int64_t C,
+                       int64_t slices, hipStream_t s);
+hipError_t relu_bn_bwd_sums(const BnBehind& b, const float* dy, float* dr, hipStream_t s);
 hipError_t bn_bwd(const float* x, const float* gamma, float* stats, const float* dy, float* dx,
                   float* dgamma, float* dbeta, int64_t rows, int64_t C, int64_t slices,
                   hipStream_t s);

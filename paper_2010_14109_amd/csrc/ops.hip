@@ -235,17 +235,29 @@ struct SliceMap {
   __device__ int64_t end(int64_t s) const { return min(rows, (s + 1) * len); }
 };
 
+// A normalised value.  Explicit fma, so that every kernel gets the same bits: the sign decides
+// a ReLU's mask in the forward and again in the backward.
+__device__ inline float bn_value(float x, float mean, float invstd, float gamma, float beta) {
+  return fmaf((x - mean) * invstd, gamma, beta);
+}
+
 // per (slice, channel): sums of (x - shift) and (x - shift)^2, shift = x[row 0]
-// (mode 0), or of dy and dy * xhat (mode 1)
+// (mode 0), or of dy and dy * xhat (mode 1).  Mode 2 is mode 1 behind a ReLU of
+// the normalised value: dy is zeroed where that is not positive, and stored to
+// dr.  Bound by HBM: three passes over a tensor instead of the five of a ReLU
+// launch and mode 1 (125 + 94 -> 121 us at 205 MB, 15.1 + 11.7 -> 22.3 at
+// 33.5 MB, where too few workgroups are in flight for the stores).
 template <int MODE>
 __global__ void bn_partials(const float* __restrict__ x, const float* __restrict__ dy,
-                            float* __restrict__ stats, SliceMap sm, int64_t C) {
+                            float* __restrict__ stats, SliceMap sm, int64_t C,
+                            const float* __restrict__ gamma, const float* __restrict__ beta,
+                            float* __restrict__ dr) {
   __shared__ float sa[16][64], sb[16][64];
   const int s = blockIdx.x;
   const int rl = threadIdx.x >> 4, cl = threadIdx.x & 15;
   const int64_t c0 = (int64_t)blockIdx.y * 64 + cl * 4;
   float a[4] = {0, 0, 0, 0}, b[4] = {0, 0, 0, 0};
-  float sh[4] = {0, 0, 0, 0}, inv[4] = {0, 0, 0, 0};
+  float sh[4] = {0, 0, 0, 0}, inv[4] = {0, 0, 0, 0}, ga[4] = {0, 0, 0, 0}, be[4] = {0, 0, 0, 0};
   for (int e = 0; e < 4; ++e) {
     const int64_t c = c0 + e;
     if (c < C) {
@@ -254,9 +266,17 @@ __global__ void bn_partials(const float* __restrict__ x, const float* __restrict
       } else {
         sh[e] = stats[c];
         inv[e] = stats[C + c];
+        if (MODE == 2) {
+          ga[e] = gamma[c];
+          be[e] = beta[c];
+        }
       }
     }
   }
+  auto mask = [&](const float (&xv)[4], float (&gv)[4]) {
+    for (int e = 0; e < 4; ++e)
+      gv[e] = bn_value(xv[e], sh[e], inv[e], ga[e], be[e]) > 0.f ? gv[e] : 0.f;
+  };
   const bool vec = (C % 4 == 0) && c0 + 3 < C;
   auto add = [&](const float (&xv)[4], const float (&gv)[4]) {
     for (int e = 0; e < 4; ++e) {
@@ -280,14 +300,19 @@ __global__ void bn_partials(const float* __restrict__ x, const float* __restrict
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         t[k] = *reinterpret_cast<const float4*>(&x[(r + 16 * k) * C + c0]);
-        if (MODE == 1) u[k] = *reinterpret_cast<const float4*>(&dy[(r + 16 * k) * C + c0]);
+        if (MODE != 0) u[k] = *reinterpret_cast<const float4*>(&dy[(r + 16 * k) * C + c0]);
       }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const float xv[4] = {t[k].x, t[k].y, t[k].z, t[k].w};
         float gv[4] = {0, 0, 0, 0};
-        if (MODE == 1) {
+        if (MODE != 0) {
           gv[0] = u[k].x; gv[1] = u[k].y; gv[2] = u[k].z; gv[3] = u[k].w;
+        }
+        if (MODE == 2) {
+          mask(xv, gv);
+          *reinterpret_cast<float4*>(&dr[(r + 16 * k) * C + c0]) =
+              make_float4(gv[0], gv[1], gv[2], gv[3]);
         }
         add(xv, gv);
       }
@@ -298,15 +323,24 @@ __global__ void bn_partials(const float* __restrict__ x, const float* __restrict
     if (vec) {
       const float4 t = *reinterpret_cast<const float4*>(&x[r * C + c0]);
       xv[0] = t.x; xv[1] = t.y; xv[2] = t.z; xv[3] = t.w;
-      if (MODE == 1) {
+      if (MODE != 0) {
         const float4 u = *reinterpret_cast<const float4*>(&dy[r * C + c0]);
         gv[0] = u.x; gv[1] = u.y; gv[2] = u.z; gv[3] = u.w;
+      }
+      if (MODE == 2) {
+        mask(xv, gv);
+        *reinterpret_cast<float4*>(&dr[r * C + c0]) = make_float4(gv[0], gv[1], gv[2], gv[3]);
       }
     } else {
       for (int e = 0; e < 4; ++e) {
         const int64_t c = c0 + e;
         xv[e] = c < C ? x[r * C + c] : 0.f;
-        if (MODE == 1) gv[e] = c < C ? dy[r * C + c] : 0.f;
+        if (MODE != 0) gv[e] = c < C ? dy[r * C + c] : 0.f;
+      }
+      if (MODE == 2) {
+        mask(xv, gv);
+        for (int e = 0; e < 4; ++e)
+          if (c0 + e < C) dr[r * C + c0 + e] = gv[e];
       }
     }
     add(xv, gv);
@@ -474,38 +508,54 @@ hipError_t bn_reduce(const float* x, float* stats, float* dgamma, float* dbeta, 
   return hipGetLastError();
 }
 
-// forward: y = (x - mean) invstd gamma + beta; backward:
-// dx = gamma invstd (dy - dbeta / rows - xhat dgamma / rows)
+// forward (mode 0): y = (x - mean) invstd gamma + beta, with a ReLU behind it in mode 2; backward
+// (mode 1): dx = gamma invstd (dy - dbeta / rows - xhat dgamma / rows).  Bound by HBM.  vec: four
+// channels a lane (C % 4 == 0, 16-byte aligned arrays); the lane's channel moves by the grid's
+// stride modulo C, so that only the first one takes a division (205 MB: APPLY_FIGS).
 template <int MODE>
 __global__ void bn_apply(const float* __restrict__ x, const float* __restrict__ dy,
                          const float* __restrict__ stats, const float* __restrict__ gamma,
                          const float* __restrict__ beta, const float* __restrict__ dgamma,
                          float* __restrict__ out, int64_t rows, int64_t C, bool vec) {
   const int64_t n = rows * C;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t stride = gridDim.x * blockDim.x;   // at most 2^22
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   const float inv_rows = 1.f / (float)rows;
-  auto f = [&](float xv, float gv, int64_t c) {
-    const float mean = stats[c], invstd = stats[C + c];
-    const float xh = (xv - mean) * invstd;
-    if (MODE == 0) return xh * gamma[c] + beta[c];
-    return gamma[c] * invstd * (gv - beta[c] * inv_rows - xh * dgamma[c] * inv_rows);
+  auto f = [&](float xv, float gv, float mean, float invstd, float g, float b, float dg) {
+    if (MODE == 1)
+      return g * invstd * (gv - b * inv_rows - (xv - mean) * invstd * dg * inv_rows);
+    const float v = bn_value(xv, mean, invstd, g, b);
+    return MODE == 0 || v > 0.f ? v : 0.f;
   };
   int64_t done = 0;
   if (vec) {
+    const float4 z = make_float4(0, 0, 0, 0);
+    const float4* const mean4 = reinterpret_cast<const float4*>(stats);
+    const float4* const inv4 = reinterpret_cast<const float4*>(stats + C);
+    const float4* const g4 = reinterpret_cast<const float4*>(gamma);
+    const float4* const b4 = reinterpret_cast<const float4*>(beta);
+    const float4* const d4 = reinterpret_cast<const float4*>(dgamma);
     const int64_t n4 = n / 4;
+    const int64_t C4 = C / 4;
+    int64_t c = C4 > i ? i : i % (uint32_t)C4;
+    const int64_t step = C4 > stride ? stride : stride % (uint32_t)C4;
     for (int64_t j = i; j < n4; j += stride) {
-      const int64_t c = (j * 4) % C;
       const float4 xv = reinterpret_cast<const float4*>(x)[j];
-      float4 gv = make_float4(0, 0, 0, 0);
-      if (MODE == 1) gv = reinterpret_cast<const float4*>(dy)[j];
-      reinterpret_cast<float4*>(out)[j] = make_float4(f(xv.x, gv.x, c), f(xv.y, gv.y, c + 1),
-                                                      f(xv.z, gv.z, c + 2), f(xv.w, gv.w, c + 3));
+      const float4 gv = MODE == 1 ? reinterpret_cast<const float4*>(dy)[j] : z;
+      const float4 m = mean4[c], s = inv4[c], g = g4[c], b = b4[c], d = MODE == 1 ? d4[c] : z;
+      reinterpret_cast<float4*>(out)[j] =
+          make_float4(f(xv.x, gv.x, m.x, s.x, g.x, b.x, d.x), f(xv.y, gv.y, m.y, s.y, g.y, b.y, d.y),
+                      f(xv.z, gv.z, m.z, s.z, g.z, b.z, d.z), f(xv.w, gv.w, m.w, s.w, g.w, b.w, d.w));
+      c += step;
+      c -= c >= C4 ? C4 : 0;
     }
     done = n4 * 4;
   }
-  for (int64_t j = done + i; j < n; j += stride)
-    out[j] = f(x[j], MODE == 1 ? dy[j] : 0.f, j % C);
+  for (int64_t j = done + i; j < n; j += stride) {
+    const int64_t c = j % C;
+    out[j] = f(x[j], MODE == 1 ? dy[j] : 0.f, stats[c], stats[C + c], gamma[c], beta[c],
+               MODE == 1 ? dgamma[c] : 0.f);
+  }
 }
 
 // ---------------------------------------------------------------- pooling
@@ -888,31 +938,48 @@ hipError_t softmax_ce(const float* logits, const int32_t* labels, float* loss, f
 }
 
 hipError_t bn_fwd(const float* x, const float* gamma, const float* beta, float* y, float* stats,
-                  int64_t rows, int64_t C, int64_t slices, hipStream_t s) {
+                  int64_t rows, int64_t C, int64_t slices, bool relu, hipStream_t s) {
   SliceMap sm{rows, slices, (rows + slices - 1) / slices};
   const unsigned cg = (unsigned)((C + 63) / 64);
   hipLaunchKernelGGL(bn_partials<0>, dim3((unsigned)slices, cg), dim3(TPB), 0, s, x, nullptr,
-                     stats, sm, C);
+                     stats, sm, C, nullptr, nullptr, nullptr);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if ((e = bn_reduce<0>(x, stats, nullptr, nullptr, rows, C, slices, s)) != hipSuccess) return e;
-  const bool vec = C % 4 == 0 && aligned16(x) && aligned16(y);
-  hipLaunchKernelGGL(bn_apply<0>, dim3(grid_for((rows * C + 3) / 4)), dim3(TPB), 0, s, x, nullptr,
-                     stats, gamma, beta, nullptr, y, rows, C, vec);
+  const bool vec = C % 4 == 0 && aligned16(x) && aligned16(y) && aligned16(stats) &&
+                   aligned16(gamma) && aligned16(beta);
+  const dim3 grid(grid_for((rows * C + 3) / 4));
+  if (relu)
+    hipLaunchKernelGGL(bn_apply<2>, grid, dim3(TPB), 0, s, x, nullptr, stats, gamma, beta, nullptr,
+                       y, rows, C, vec);
+  else
+    hipLaunchKernelGGL(bn_apply<0>, grid, dim3(TPB), 0, s, x, nullptr, stats, gamma, beta, nullptr,
+                       y, rows, C, vec);
+  return hipGetLastError();
+}
+
+hipError_t bn_bwd_sums(const float* x, float* stats, const float* dy, int64_t rows, int64_t C,
+                       int64_t slices, hipStream_t s) {
+  SliceMap sm{rows, slices, (rows + slices - 1) / slices};
+  hipLaunchKernelGGL(bn_partials<1>, dim3((unsigned)slices, (unsigned)((C + 63) / 64)), dim3(TPB),
+                     0, s, x, dy, stats, sm, C, nullptr, nullptr, nullptr);
+  return hipGetLastError();
+}
+
+hipError_t relu_bn_bwd_sums(const BnBehind& b, const float* dy, float* dr, hipStream_t s) {
+  SliceMap sm{b.rows, b.slices, (b.rows + b.slices - 1) / b.slices};
+  hipLaunchKernelGGL(bn_partials<2>, dim3((unsigned)b.slices, (unsigned)((b.C + 63) / 64)),
+                     dim3(TPB), 0, s, b.x, dy, b.stats, sm, b.C, b.gamma, b.beta, dr);
   return hipGetLastError();
 }
 
 hipError_t bn_bwd(const float* x, const float* gamma, float* stats, const float* dy, float* dx,
                   float* dgamma, float* dbeta, int64_t rows, int64_t C, int64_t slices,
                   hipStream_t s) {
-  SliceMap sm{rows, slices, (rows + slices - 1) / slices};
-  const unsigned cg = (unsigned)((C + 63) / 64);
-  hipLaunchKernelGGL(bn_partials<1>, dim3((unsigned)slices, cg), dim3(TPB), 0, s, x, dy, stats, sm,
-                     C);
-  hipError_t e = hipGetLastError();
+  hipError_t e = bn_reduce<1>(x, stats, dgamma, dbeta, rows, C, slices, s);
   if (e != hipSuccess) return e;
-  if ((e = bn_reduce<1>(x, stats, dgamma, dbeta, rows, C, slices, s)) != hipSuccess) return e;
-  const bool vec = C % 4 == 0 && aligned16(x) && aligned16(dy) && aligned16(dx);
+  const bool vec = C % 4 == 0 && aligned16(x) && aligned16(dy) && aligned16(dx) &&
+                   aligned16(stats) && aligned16(gamma) && aligned16(dgamma) && aligned16(dbeta);
   // backward uses beta's slot for dbeta: dx = gamma invstd (dy - dbeta/rows - xhat dgamma/rows)
   hipLaunchKernelGGL(bn_apply<1>, dim3(grid_for((rows * C + 3) / 4)), dim3(TPB), 0, s, x, dy,
                      stats, gamma, dbeta, dgamma, dx, rows, C, vec);

@@ -186,6 +186,73 @@ static void first_last_use(const std::vector<Var>& vars, const std::vector<Fn>& 
     }
 }
 
+// Batch normalisations and the ReLUs behind them that can share their passes over memory in the
+// in-core program, where a variable keeps one address from its first use to its last.
+//
+// Forward: RELU_FWD right behind the BN_FWD whose Y it reads runs both in its own place and Y is
+// never written.  Nothing may read Y afterwards, and whatever BN_FWD uses has to be there still:
+// a TEMP that BN_FWD uses last has given its memory up, perhaps to the ReLU's output.
+// Backward: RELU_BWD right before the BN_BWD that reads its dX also takes that function's sums,
+// with the mask recomputed from X: the ReLU's Y has to come from a RELU_FWD of the Y of a BN_FWD
+// of the same X, gamma and stats, which nothing has written since (nor beta); the ReLU's dY is
+// not the stats that the sums go to.
+// Traffic in passes over a tensor: forward 5 -> 3, backward 8 -> 6.
+void plan_joins(const std::vector<Var>& vars, const std::vector<Fn>& fns, JoinPlan* out) {
+  const int64_t N = (int64_t)fns.size();
+  out->join.assign(N, Join::kNone);
+  out->bn_fwd.assign(N, -1);
+  std::vector<int64_t> fu, lu;
+  first_last_use(vars, fns, &fu, &lu);
+  auto use = [&](int64_t i, int64_t v) -> uint8_t {
+    for (const FnVar& fv : fns[i].vars)
+      if (fv.var == v) return fv.access;
+    return 0;
+  };
+  auto alive = [&](int64_t v, int64_t i) {
+    return vars[v].kind != OOC_TEMP || (fu[v] <= i && lu[v] >= i);
+  };
+  // the last function before i that writes v, or -1
+  auto writer = [&](int64_t v, int64_t i) {
+    for (--i; i >= 0; --i)
+      if (use(i, v) & OOC_W) return i;
+    return (int64_t)-1;
+  };
+  for (int64_t i = 1; i < N; ++i) {
+    const Fn &f = fns[i - 1], &g = fns[i];
+    if (f.op == OOC_OP_BN_FWD && g.op == OOC_OP_RELU_FWD && g.vars[0].var == f.vars[3].var &&
+        out->join[i - 1] == Join::kNone) {
+      const int64_t y = f.vars[3].var;
+      bool ok = vars[y].kind == OOC_TEMP && use(i - 1, g.vars[1].var) == 0;
+      for (const FnVar& fv : f.vars) ok = ok && alive(fv.var, i);
+      for (int64_t k = i + 1; ok && k < N; ++k) {
+        const uint8_t u = use(k, y);
+        if (u & OOC_R) ok = false;
+        else if (u) break;
+      }
+      if (!ok) continue;
+      out->join[i - 1] = Join::kBnBeforeRelu;
+      out->join[i] = Join::kReluOfBn;
+      out->bn_fwd[i] = i - 1;
+    } else if (f.op == OOC_OP_RELU_BWD && g.op == OOC_OP_BN_BWD &&
+               g.vars[3].var == f.vars[2].var && f.vars[1].var != g.vars[2].var) {
+      const int64_t k = writer(f.vars[0].var, i - 1);
+      if (k < 0 || fns[k].op != OOC_OP_RELU_FWD || fns[k].vars[1].var != f.vars[0].var) continue;
+      const int64_t b = writer(fns[k].vars[0].var, k);
+      if (b < 0 || fns[b].op != OOC_OP_BN_FWD) continue;
+      const Fn& n = fns[b];
+      bool ok = n.vars[3].var == fns[k].vars[0].var && n.vars[0].var == g.vars[0].var &&
+                n.vars[1].var == g.vars[1].var && n.vars[4].var == g.vars[2].var &&
+                n.attrs[0] == g.attrs[0] && n.attrs[1] == g.attrs[1];
+      for (const int j : {0, 1, 2, 4})
+        ok = ok && alive(n.vars[j].var, i - 1) && writer(n.vars[j].var, i) <= b;
+      if (!ok) continue;
+      out->join[i - 1] = Join::kReluBwdSums;
+      out->join[i] = Join::kBnSumsDone;
+      out->bn_fwd[i - 1] = b;
+    }
+  }
+}
+
 void build_incore(const std::vector<Var>& vars, const std::vector<Fn>& fns, uint64_t chunk,
                   Schedule* out) {
   std::vector<int64_t> fu, lu;

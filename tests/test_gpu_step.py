@@ -86,6 +86,54 @@ def test_step_matches_oracle_and_is_budget_independent(spec):
                 assert outs[name].tobytes() == outs0[name].tobytes(), (name, B, W, policy, wait)
 
 
+def bn_relu_spec(hw, width, last):
+    """Batch norms in front of ReLUs that can share their passes and some that cannot: "n2" is
+    also read by the addition, "n3" has no ReLU; "r4" is read by two layers; the last one's
+    channel count may be odd."""
+    def conv(name, src, cin, cout):
+        return {"name": name, "op": "conv", "in": [src], "cin": cin, "cout": cout, "k": 3,
+                "stride": 1, "pad": 1}
+
+    def bn(name, src, c):
+        return {"name": name, "op": "bn", "in": [src], "c": c}
+
+    def relu(name, src):
+        return {"name": name, "op": "relu", "in": [src]}
+
+    layers = [conv("c1", "x", 3, width), bn("n1", "c1", width), relu("r1", "n1"),
+              conv("c2", "r1", width, width), bn("n2", "c2", width), relu("r2", "n2"),
+              conv("c3", "r2", width, width), bn("n3", "c3", width),
+              {"name": "a3", "op": "add", "in": ["n3", "n2"]}, relu("r3", "a3"),
+              bn("n4", "r3", width), relu("r4", "n4"), conv("c4", "r4", width, width),
+              {"name": "a4", "op": "add", "in": ["c4", "r4"]},
+              conv("c5", "a4", width, last), bn("n5", "c5", last), relu("r5", "n5"),
+              {"name": "gap", "op": "avgpool", "in": ["r5"]},
+              {"name": "fc", "op": "linear", "in": ["gap"], "in_features": last,
+               "out_features": 5}]
+    return {"name": f"bn_relu_{hw}_{width}_{last}", "input": [3, hw, hw, 3], "classes": 5,
+            "layers": layers, "logits": "fc", "optimizer": {"lr": 0.01, "momentum": 0.9}}
+
+
+@pytest.mark.parametrize("hw,width,last", [(5, 4, 1), (8, 32, 7), (9, 68, 64), (13, 20, 65)])
+def test_joined_batch_norm_and_relu_equal_the_single_functions(hw, width, last):
+    """In core a batch norm and its ReLU share kernels, out of core every function runs alone:
+    the same bits, over steps that start from what the ones before left."""
+    spec = bn_relu_spec(hw, width, last)
+    x, labels = synth.make_inputs(spec, 0)
+    params = synth.make_params(spec, 1)
+    for name in params:   # signs of both kinds, and channels whose every value is cut off
+        if name.endswith((".gamma", ".beta")):
+            params[name] = np.random.default_rng(len(name)).standard_normal(
+                params[name].shape).astype(np.float32)
+    loss0, outs0, _ = run_net(spec, x, labels, params, chunk=4096, steps=3)
+    b, k, f = as_schedule_input(lowering(spec, keep_grads=True))
+    B = S.working_set_max(b, f, 4096)
+    loss, outs, _ = run_net(spec, x, labels, params, budget=B, window=B // 2, chunk=4096, steps=3)
+    assert np.float32(loss).tobytes() == np.float32(loss0).tobytes()
+    for name in outs0:
+        assert outs[name].tobytes() == outs0[name].tobytes(), name
+
+
 def test_full_size_mlp_matches_oracle():
     """The 8-layer, width-1024 MLP at batch 256 with a budget of 40% of its in-core peak."""
     spec = synth.workload("mlp")
