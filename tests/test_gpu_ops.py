@@ -410,6 +410,30 @@ def test_softmax_ce(N, C):
     assert rel_err(dZ, rdZ) < TOL or np.abs(dZ - rdZ).max() < 1e-7
 
 
+@pytest.mark.parametrize("C", [1, 8, 9, 16, 17, 32, 33, 64, 65, 256, 257, 1024, 1025, 4096, 4097, 8192,
+                               8193, 16384, 16385, 32768, 32769])
+def test_softmax_ce_row_lengths(C):
+    """Both sides of every limit of the row kernels, values of -inf, a constant row, a row count
+    that leaves a workgroup partly empty.  The exponentials' arguments reach 25 and carry half an
+    ulp of that, 1e-6; the sums are short chains."""
+    N = 5
+    Z = f32(N, C, scale=3.0)
+    Z[1] = 2.5
+    Z[2, : C // 2] = -np.inf
+    y = rng.integers(C // 2, C, N).astype(np.int32)
+    print(f"softmax_ce C={C}", flush=True)
+    (_, _, loss, dZ) = run_fn("softmax_ce", [(Z, ooc.R), (y, ooc.R), (((N + 1,), "f32"), ooc.W),
+                                             (((N, C), "f32"), ooc.W)], [N, C])
+    z = d(Z)
+    e = np.exp(z - z.max(1, keepdims=True))
+    p = e / e.sum(1, keepdims=True)
+    rows = -np.log(p[np.arange(N), y])
+    p[np.arange(N), y] -= 1
+    assert np.abs(loss[:N] - rows).max() <= 4e-6 * max(1.0, np.abs(rows).max())
+    assert abs(loss[N] - rows.mean()) <= 4e-6 * max(1.0, np.abs(rows).max())
+    assert np.abs(dZ * N - p).max() <= 4e-6 and (C == 1 or rel_err(dZ, p / N) <= 4e-6)
+
+
 def test_softmax_ce_out_of_range_label():
     N, C = 4, 6
     Z = f32(N, C)
