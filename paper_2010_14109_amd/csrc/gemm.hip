@@ -95,6 +95,9 @@ __device__ inline __amdgpu_buffer_rsrc_t buffer(const float* p, int64_t values) 
 __device__ inline float4 ldb(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
 }
+__device__ inline float ldb1(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
 
 // What masked lanes of the general views load (never written).
 __device__ __attribute__((aligned(16))) float g_zero[64] = {};
@@ -373,12 +376,15 @@ struct MatMFar : RowM<E> {
 // Loader modes of the convolution views.  Row-of-k views: TAP when the
 // reduced channel count is a multiple of 32 (a K tile lies inside one filter
 // tap, uniform over the workgroup), VEC4 when it is a multiple of 4 (each lane
-// splits its own k index, four consecutive channels per load), SCALAR (64-bit
-// addresses, one per value) otherwise.  Row-of-m views: VEC4 when each float4
-// lies in one tap, SCALAR otherwise.  TAP and VEC4 take byte offsets from the
-// first image row that the tile can touch; the launchers check that they fit
-// (window_fits).
-enum { SCALAR = 0, VEC4 = 1, TAP = 2 };
+// splits its own k index, four consecutive channels per load), VEC1 (one load
+// per value) otherwise.  Row-of-m views: VEC4 when each float4 lies in one tap,
+// VEC1 otherwise.  These take byte offsets from the first image row that the
+// tile can touch; the launchers check that they fit (window_fits).  SCALAR, a
+// 64-bit address per value, is for images too large for that and, among the
+// gradient taps, for channel counts that are not multiples of 4.  7 x 7 stride 2
+// on 64 x 224 x 224 x 3, 64-bit addresses and VEC1: forward 208 and 175 us,
+// filter gradient 240 and 221.
+enum { SCALAR = 0, VEC4 = 1, TAP = 2, VEC1 = 3 };
 
 __device__ inline int clampi(int v, int lo, int hi) { return min(max(v, lo), hi); }
 
@@ -437,6 +443,23 @@ struct ConvPatch : RowK<E> {
       for (int j = 0; j < Base::kN; ++j)
         r[j] = make_float4(at(j, kk, kend), at(j, kk + 1, kend), at(j, kk + 2, kend),
                            at(j, kk + 3, kend));
+    } else if constexpr (MODE == VEC1) {
+      const auto b = buffer(x, k0 < kend ? int64_t(1) << 29 : 0);
+      float v[Base::kN][4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int rr = dSC.div(kk + e);
+        const int rem = kk + e - rr * (int)dSC.d;
+        const int s = dC.div(rem);
+        const int toff = ((rr * W + s) * C + rem - s * C) * 4;
+#pragma unroll
+        for (int j = 0; j < Base::kN; ++j) {
+          const bool ok = (kk + e < kend) & inside(h_[j] + rr, H) & inside(w_[j] + s, W);
+          v[j][e] = ldb1(b, ok ? (uint32_t)(base_[j] + toff) : kNone);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < Base::kN; ++j) r[j] = make_float4(v[j][0], v[j][1], v[j][2], v[j][3]);
     } else {
       int rr, s, c;
       bool kin = true;
@@ -598,13 +621,13 @@ struct ConvFilterTap : RowM<E> {
 // Convolution filter gradient, B = input patches along the pixel axis:
 // B[kk = (n, p, q)][col = (r, s, c)] = X[n][p st - pad + r][q st - pad + s][c]
 // (row-of-m).  A lane's columns are clamped to the matrix, then split into
-// taps at set-up: one per float4 (VEC4) or one per value (SCALAR).  A lane's
+// taps at set-up: one per float4 (VEC4) or one per value.  A lane's
 // kR pixels are consecutive: the first one's position is split from its index,
 // the others step from it.
 template <int E, int MODE>
 struct ConvPixelPatch : RowM<E> {
   using Base = RowM<E>;
-  using Off = std::conditional_t<MODE == VEC4, int, int64_t>;
+  using Off = std::conditional_t<MODE == SCALAR, int64_t, int>;
   static constexpr int kPer = MODE == VEC4 ? 1 : 4;   // taps per float4
   static constexpr int kT = kPer * Base::kItems;
   const float* x;
@@ -635,8 +658,8 @@ struct ConvPixelPatch : RowM<E> {
     q = rem - p * (int)dQ.d;
   }
   __device__ void fetch(int64_t k0, int64_t kend, float4 (&r)[Base::kN]) const {
-    int n0 = 0, hb0 = 0;      // VEC4: the image row that offsets count from
-    if constexpr (MODE == VEC4) {
+    int n0 = 0, hb0 = 0;      // the image row that 32-bit offsets count from
+    if constexpr (MODE != SCALAR) {
       int p0, q0;
       split(k0 < kend ? (int)k0 : 0, n0, p0, q0);
       hb0 = clampi(p0 * st - pad, 0, H - 1);
@@ -662,7 +685,10 @@ struct ConvPixelPatch : RowM<E> {
           for (int e = 0; e < 4; ++e) {
             const int u = 4 * i + e;
             const bool ok = kin & inside(hb + r_[u], H) & inside(wb + s_[u], W);
-            v[e] = *(ok ? x + po + toff_[u] : g_zero);
+            if constexpr (MODE == VEC1)
+              v[e] = ldb1(b, ok ? (uint32_t)(po + toff_[u]) * 4u : kNone);
+            else
+              v[e] = *(ok ? x + po + toff_[u] : g_zero);
           }
           r[i * Base::kR + j] = make_float4(v[0], v[1], v[2], v[3]);
         }
@@ -1117,6 +1143,7 @@ hipError_t dispatch_shape(FA fa, FB fb, float* c, OM om, int64_t slice_stride, i
 
 template <int E> using ConvPatchT = ConvPatch<E, TAP>;
 template <int E> using ConvPatchV = ConvPatch<E, VEC4>;
+template <int E> using ConvPatch1 = ConvPatch<E, VEC1>;
 template <int E> using ConvPatchS = ConvPatch<E, SCALAR>;
 template <int E> using ConvGradTapT = ConvGradTap<E, TAP>;
 template <int E> using ConvGradTapV = ConvGradTap<E, VEC4>;
@@ -1124,6 +1151,7 @@ template <int E> using ConvGradTapS = ConvGradTap<E, SCALAR>;
 template <int E> using ConvFilterTapT = ConvFilterTap<E, TAP>;
 template <int E> using ConvFilterTapG = ConvFilterTap<E, VEC4>;
 template <int E> using ConvPixelPatchV = ConvPixelPatch<E, VEC4>;
+template <int E> using ConvPixelPatch1 = ConvPixelPatch<E, VEC1>;
 template <int E> using ConvPixelPatchS = ConvPixelPatch<E, SCALAR>;
 
 // the GEMM sizes of the convolution views index with 32-bit arithmetic
@@ -1316,8 +1344,9 @@ hipError_t conv_fwd(const float* X, const float* W, float* Y, const ConvShape& c
     a.dS = FastDiv::make(c.S); a.dSC = FastDiv::make(c.S * c.C);
   };
   const auto fb = dense(W, K, K);
-  const bool near = c.C % 4 == 0 && K <= kMaxLd &&
+  const bool fits = K <= kMaxLd &&
                     window_fits(256, c.P, c.Q, c.stride, c.R + 2 * c.pad, c.H, c.W, c.C);
+  const bool near = fits && c.C % 4 == 0;
   if (N <= 32 && near) {
     // at most 32 output channels: 256 x 32 tiles, no empty columns; 128 x 32 when there are
     // fewer 256-row tiles than CUs, so that twice as many workgroups share the chip
@@ -1333,6 +1362,7 @@ hipError_t conv_fwd(const float* X, const float* W, float* Y, const ConvShape& c
   if (near && c.C % 32 == 0)
     return dispatch_dense<ConvPatchT, MatK, false>(fa, fb, Y, N, nullptr, M, N, K, 1, s);
   if (near) return dispatch_dense<ConvPatchV, MatK, false>(fa, fb, Y, N, nullptr, M, N, K, 1, s);
+  if (fits) return dispatch_dense<ConvPatch1, MatK, false>(fa, fb, Y, N, nullptr, M, N, K, 1, s);
   if (K <= kMaxLd)
     return dispatch_dense<ConvPatchS, MatK, false>(fa, fb, Y, N, nullptr, M, N, K, 1, s);
   return dispatch_dense<ConvPatchS, MatKFar, false>(fa, fb, Y, N, nullptr, M, N, K, 1, s);
@@ -1408,8 +1438,9 @@ hipError_t conv_bwd_w(const float* X, const float* dY, float* dW, float* part, i
   };
   const DenseOut om{N};
   // a K tile covers 32 pixels; twice that covers the offsets of a lane's steps past the tile
-  const bool near = c.C % 4 == 0 && c.K <= kMaxLd &&
+  const bool fits = c.K <= kMaxLd &&
                     window_fits(64, c.P, c.Q, c.stride, c.R + 2 * c.pad, c.H, c.W, c.C);
+  const bool near = fits && c.C % 4 == 0;
   const WgradTile tile = wgrad_tile(M, N, c.C);
   hipError_t e;
   if (near && tile == WgradTile::k32x256)   // at most 32 output channels: no empty tile rows
@@ -1422,6 +1453,8 @@ hipError_t conv_bwd_w(const float* X, const float* dY, float* dW, float* part, i
                                           s);
   else if (near)
     e = dispatch_dense<MatM, ConvPixelPatchV, false>(fa, fb, out, N, nullptr, M, N, K, slices, s);
+  else if (fits)
+    e = dispatch_dense<MatM, ConvPixelPatch1, false>(fa, fb, out, N, nullptr, M, N, K, slices, s);
   else if (c.K <= kMaxLd)
     e = dispatch_dense<MatM, ConvPixelPatchS, false>(fa, fb, out, N, nullptr, M, N, K, slices, s);
   else

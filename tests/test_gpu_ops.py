@@ -220,6 +220,16 @@ def test_conv(shape):
         assert rel_err(dX, ops.conv_bwd_x(d(Wt), d(G), X.shape, st, pd)) < TOL
 
 
+# one load per value (channels not a multiple of 4): a tile over many images, over part of a row,
+# strides past the image, padding wider than the tap, every tile shape, ragged K tiles
+@pytest.mark.parametrize("shape", [(40, 2, 3, 1, 8, 3, 1, 1), (3, 5, 400, 3, 64, 7, 2, 3),
+                                   (9, 11, 7, 5, 130, 3, 2, 2), (2, 33, 31, 6, 64, 5, 3, 0),
+                                   (1, 4, 4, 7, 260, 4, 1, 3), (2, 66, 70, 3, 256, 3, 1, 1)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_conv_one_load_per_value(shape):
+    test_conv(shape)
+
+
 def test_conv_bwd_x_fills_unreached_classes():
     """A 1 x 1 stride-2 input gradient reaches one stride class of four; the other pixels must
     be written as zeros, not left as they were.  Out of core at the smallest budget the output
