@@ -551,6 +551,21 @@ def test_embedding(B, T, V, dm):
     assert rel_err(dE, rdE) < TOL and rel_err(dpos, rdpos) < TOL
 
 
+@pytest.mark.parametrize("B,T,V,dm", [(1, 1, 1, 4), (1, 511, 3, 68), (3, 171, 5, 1024), (2, 513, 7, 1025),
+                                      (1, 1100, 2, 2050)])
+def test_embedding_gradient_adds_in_token_order(B, T, V, dm):
+    """Both sides of a scan block's tokens and of a pass's columns: the same bits as float32
+    additions token by token."""
+    ids = rng.integers(0, V, (B, T)).astype(np.int32)
+    G = f32(B * T, dm)
+    (_, _, dE, _) = run_fn("embed_bwd", [(ids, ooc.R), (G, ooc.R), (((V, dm), "f32"), ooc.W),
+                                         (((T, dm), "f32"), ooc.W)], [B, T, V, dm])
+    ref = np.zeros((V, dm), np.float32)
+    for r, v in enumerate(ids.reshape(-1)):
+        ref[v] += G[r]
+    assert np.array_equal(dE, ref)
+
+
 def test_embedding_out_of_range_id():
     B, T, V, dm = 1, 3, 5, 64
     ids = np.array([[0, 7, -2]], dtype=np.int32)
