@@ -6,6 +6,12 @@ ordinary step.  It executes the functions of ``oracle.lower`` in order, in
 the given dtype (float64 for parity), and returns every variable's final
 value, so tests can compare the loss, parameter gradients and updated
 parameters with the device.
+
+A ReLU and a max pool choose by comparing values, and where two values almost
+tie, rounding decides the choice, which then moves gradients by far more than
+rounding.  ``decisions`` replaces what the backward functions read of such a
+choice (a ReLU's output, a max pool's index) by the values given, so that two
+evaluations are compared under the same choices.
 """
 
 from __future__ import annotations
@@ -15,12 +21,15 @@ import numpy as np
 from . import ops
 
 
-def run(reg, x, labels, params, state=None, dtype=np.float64):
+def run(reg, x, labels, params, state=None, dtype=np.float64, decisions=None):
     """One step.  ``params`` / ``state``: {name: array}.  Returns {var name: array}.
 
     ``state`` holds momentum buffers by name (``m:<param>``); missing ones start at 0.
+    ``decisions``: {variable name: array}, read by the backward of the ReLU with that output
+    and of the max pool with that index variable instead of the step's own.
     """
     state = state or {}
+    decisions = decisions or {}
     names = [v["name"] for v in reg["vars"]]
     env = {}
     for v in reg["vars"]:
@@ -87,11 +96,12 @@ def run(reg, x, labels, params, state=None, dtype=np.float64):
             env[dX], env[dg], env[dbt] = ops.bn_bwd(g(X), g(gm), mean, invstd, g(dY))
         elif op == "relu_bwd":
             Y, dY, dX = vs
-            env[dX] = ops.relu_bwd(g(Y), g(dY))
+            env[dX] = ops.relu_bwd(decisions.get(Y, g(Y)), g(dY))
         elif op == "maxpool_bwd":
             ix, dY, dX = vs
             shape = (a["N"], a["H"], a["W"], a["C"])
-            env[dX] = ops.maxpool_bwd(g(ix), g(dY), shape, a["k"], a["stride"], a["pad"])
+            env[dX] = ops.maxpool_bwd(decisions.get(ix, g(ix)), g(dY), shape, a["k"], a["stride"],
+                                      a["pad"])
         elif op == "avgpool_bwd":
             dY, dX = vs
             env[dX] = ops.avgpool_bwd(g(dY), (a["N"], a["H"], a["W"], a["C"]))

@@ -1,16 +1,20 @@
 """Full-size steps in the configuration ``bench.py`` times (GPU).
 
-Deep networks are ill-conditioned in fp32: near-zero ReLU inputs and
-BatchNorm over few rows make any fp32 evaluation differ from the float64
-step.  Even the oracle run in float32 differs from float64 by 3e-3 (plain CNN,
-batch 128) to 4e-2 (ResNet-50) on some gradients.  For these networks the
-bar is therefore derived from the arithmetic: for every parameter gradient,
-updated parameter and momentum buffer, the device's relative L2 error against
-float64 must be at most 1.5 times the float32 oracle's own, and its largest
-element error (relative to the largest element) at most 3 times the float32
-oracle's (neither ever has to be smaller than 1e-4; see
-``gpu_util.within_fp32_error``).  The loss, a well-conditioned forward
-quantity, must match float64 within 1e-5.
+Below a ReLU or a max pool a gradient depends on choices between values that may almost
+tie.  Rounding decides such a choice and one of them moves a single element by up to its own
+size: noise of 1e-7 on the float64 oracle's convolution outputs moves an element of
+``s3b2.c.conv.W``'s gradient (ResNet-50, batch 16) by more than twice what the float32 oracle's
+error allows, or not at all, depending on the noise's seed.  So gradients are compared under the
+device's own choices, and the choices themselves with float64's up to ties of rounding size
+(``gpu_util.check_decisions``).
+
+What remains ill-conditioned in fp32 is BatchNorm over few rows.  The bar is therefore derived
+from the arithmetic: for every parameter gradient, updated parameter and momentum buffer, the
+device's relative L2 error against float64 must be at most 1.5 times the float32 oracle's own
+under the same choices, and its largest element error (relative to the largest element) at most 3
+times the float32 oracle's (neither ever has to be smaller than 1e-4; see
+``gpu_util.within_fp32_error``).  The loss, a well-conditioned forward quantity, must match
+float64 within 1e-5.
 
 The out-of-core step must equal the in-core step bit for bit in the exact
 bench configuration (budget, window, chunk size).
@@ -20,28 +24,15 @@ import numpy as np
 import pytest
 
 import bench
-from oracle.interp import run as oracle_run
-from oracle.lower import lower
 from paper_2010_14109_amd import netdef, synth
-from tests.gpu_util import run_net, within_fp32_error
+from tests.gpu_util import check_under_own_choices, run_net
 
 pytestmark = pytest.mark.gpu
 
 
-def derived_check(spec, loss, outs):
-    reg = lower(spec, keep_grads=True)
-    x, labels = synth.make_inputs(spec, 0)
-    params = synth.make_params(spec, 1)
-    e64 = oracle_run(reg, x, labels, {k: v.astype(np.float64) for k, v in params.items()})
-    e32 = oracle_run(reg, x, labels, {k: v.astype(np.float32) for k, v in params.items()},
-                     dtype=np.float32)
+def derived_check(spec, x, labels, params, loss, outs, chunk):
+    e64, worst = check_under_own_choices(spec, x, labels, params, outs, chunk)
     assert abs(loss - e64["loss"][-1]) <= 1e-5 * abs(e64["loss"][-1])
-    worst = (0.0, 0.0)
-    for name, val in outs.items():
-        if name == "loss":
-            continue
-        l2, mx = within_fp32_error(name, val, e64[name], e32[name], 1e-4)
-        worst = (max(worst[0], l2), max(worst[1], mx))
     print(f"{spec['name']}: worst error / bound: relative L2 {worst[0]:.2f}, largest element "
           f"{worst[1]:.2f}", flush=True)
 
@@ -66,7 +57,7 @@ def test_plain_cnn_batch128_bench_config():
     for n in outs0:
         assert outs[n].tobytes() == outs0[n].tobytes(), n
     print("cnn b128: bit-identical to in-core; checking against the oracle", flush=True)
-    derived_check(spec, loss, outs)
+    derived_check(spec, x, labels, params, loss, outs, chunk)
 
 
 @pytest.mark.parametrize("batch,hw", [(16, 64), (4, 224)])
@@ -80,7 +71,7 @@ def test_resnet50_against_oracle(batch, hw):
     loss, outs, st = run_net(spec, x, labels, params, budget=plan["budget"],
                              window=plan["window"], chunk=chunk)
     assert st["pool_bytes"] <= plan["budget"]
-    derived_check(spec, loss, outs)
+    derived_check(spec, x, labels, params, loss, outs, chunk)
 
 
 def test_resnet50_batch256_bench_config_matches_incore():

@@ -20,7 +20,8 @@ from oracle.interp import run as oracle_run
 from oracle.lower import lower, as_schedule_input
 from paper_2010_14109_amd import netdef, ooc, synth
 from tests.seq_util import lowering
-from tests.gpu_util import STAGING_BYTES, persistent_host_bytes, rel_err, run_net, within_fp32_error
+from tests.gpu_util import (STAGING_BYTES, check_under_own_choices, persistent_host_bytes, rel_err,
+                            run_net)
 
 pytestmark = pytest.mark.gpu
 TOL = 1e-4
@@ -159,17 +160,14 @@ def test_full_size_cnn_matches_oracle():
     the library's default W = B/2, policy C) against the float64 oracle, and bit-identical to
     the same kernels in-core.
 
-    At this size fp32 evaluation is not well conditioned (ReLU-mask decisions near zero flip
-    between fp32 and fp64, and the batch-norm shift gradients are sums with heavy cancellation),
-    so no fp32 implementation reaches 1e-4 on every tensor.  The bound per tensor is therefore
-    the error of a plain fp32 evaluation of the same definition (the oracle run in float32), or
-    1e-4 if larger; the loss is held to 1e-4."""
+    At this size some ReLU choices tie within rounding, so gradients are compared under the
+    device's own choices, and the batch-norm shift gradients are sums with heavy cancellation, so
+    no fp32 implementation reaches 1e-4 on every tensor.  The bound per tensor is therefore the
+    error of a plain fp32 evaluation of the same definition (the oracle run in float32), or 1e-4
+    if larger; the loss is held to 1e-4."""
     spec = synth.workload("cnn")
     x, labels = synth.make_inputs(spec, 0)
     params = synth.make_params(spec, 1)
-    print("cnn full size: oracle float64 and float32", flush=True)
-    ref = oracle_step(spec, x, labels, params)
-    ref32 = oracle_run(lower(spec, keep_grads=True), x, labels, params, dtype=np.float32)
     net = netdef.Net(spec, keep_grads=True)
     chunk = 2 << 20
     p = S.incore_peak(net.var_bytes, net.var_kinds, net.fn_vars, chunk)
@@ -177,14 +175,9 @@ def test_full_size_cnn_matches_oracle():
     B = max(S.budget_for(synth.budget_fraction("cnn"), p, chunk), ws)
     print(f"cnn full size budget {B}", flush=True)
     loss, outs, st = run_net(spec, x, labels, params, budget=B, chunk=chunk)
+    assert len(outs) >= 61
+    ref, _ = check_under_own_choices(spec, x, labels, params, outs, chunk, tol=TOL)
     assert abs(loss - ref["loss"][-1]) <= TOL * abs(ref["loss"][-1])
-    checked = 0
-    for name, val in outs.items():
-        if name in ref and name != "loss" and np.linalg.norm(ref[name]) > 0:
-            r = ref[name]
-            within_fp32_error(name, val, r, ref32[name], TOL)
-            checked += 1
-    assert checked >= 60
     assert st["pool_bytes"] <= B and st["h2d_bytes"] > 0
     loss0, outs0, _ = run_net(spec, x, labels, params, chunk=chunk)
     assert np.float32(loss).tobytes() == np.float32(loss0).tobytes()

@@ -377,3 +377,28 @@ def test_tiny_transformer_gradients_by_finite_differences():
         idx, g = fd_grad(loss, arr, n=4, seed=len(name))
         got = env["d:" + name].reshape(-1)[idx]
         assert np.allclose(got, g, rtol=1e-5, atol=1e-9), name
+
+
+def test_decisions_replace_a_step_s_own_choices():
+    """A step's own choices handed back change nothing; another mask or index is what the backward
+    then uses, and only the backward."""
+    spec = {"name": "tie", "input": [2, 4, 4, 3], "classes": 5, "logits": "fc",
+            "optimizer": {"lr": 0.1, "momentum": 0.0}, "layers": [
+                {"name": "c", "op": "conv", "in": ["x"], "cin": 3, "cout": 4, "k": 3, "stride": 1,
+                 "pad": 1},
+                {"name": "r", "op": "relu", "in": ["c"]},
+                {"name": "p", "op": "maxpool", "in": ["r"], "k": 2, "stride": 2, "pad": 0},
+                {"name": "a", "op": "avgpool", "in": ["p"]},
+                {"name": "fc", "op": "linear", "in": ["a"], "in_features": 4, "out_features": 5}]}
+    reg = lower(spec, keep_grads=True)
+    x, labels = synth.make_inputs(spec, 0)
+    params = {k: v.astype(np.float64) for k, v in synth.make_params(spec, 1).items()}
+    own = run(reg, x, labels, params)
+    same = run(reg, x, labels, params, decisions={"r": own["r"], "p.idx": own["p.idx"]})
+    assert all(np.array_equal(own[n], same[n]) for n in own)
+    idx = np.full_like(own["p.idx"], 3)
+    other = run(reg, x, labels, params, decisions={"r": np.ones_like(own["r"]), "p.idx": idx})
+    assert np.array_equal(other["loss"], own["loss"])
+    dp, dr = other["d:p@a"], other["d:r@p"]
+    assert np.array_equal(dr[:, 1::2, 1::2], dp) and not dr[:, ::2].any() and not dr[:, :, ::2].any()
+    assert np.array_equal(other["d:c@r"], dr)
