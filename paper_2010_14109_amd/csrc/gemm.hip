@@ -6,9 +6,11 @@
 // and x y is the sum of the six largest piece products, accumulated in fp32:
 // a ceiling of 416 TFLOP/s instead of 157.  The result is closer to the exact
 // one than fp32 products gave, because the matrix instruction rounds its
-// accumulator once per 8 terms instead of at each: relative error at a
+// accumulator once per 16 terms instead of at each: relative error at a
 // reduction of 1024, 4.9e-7 in one accumulator and half of that with the small
-// products in a second one, against 5.7e-7.
+// products in a second one, against 5.7e-7; at 5 terms, 2.7e-8 against 4.4e-8.
+// For a single term it is not (2.60e-8 against 2.53e-8): reductions of up to
+// kFewTerms terms use fp32 products, in kernels of their own.
 // 12288 x 1024 x 4096: 0.80 ms (129 TFLOP/s) with fp32 products, 0.57 ms (180)
 // split; at that rate the card's power limit holds the clock at 1.8 GHz, and
 // a large library product in bfloat16 reaches 1280 TFLOP/s, 213 in these units.
@@ -130,6 +132,7 @@ __device__ inline void keep(T& v) {
 // the signs alternating along both directions it cancels in such sums.
 constexpr float kSplitScale = 0x1p40f, kSplitUnscale = 0x1p-80f;
 constexpr int kPieces = 3;
+constexpr int kFewTerms = 4;
 
 __device__ __forceinline__ void split2(float x, float y, float scale, uint32_t (&o)[kPieces]) {
   // (-1, 0) and (0, -1) as register operands: as constants, the compiler would encode one of them
@@ -761,11 +764,11 @@ struct WaveGrid {
 };
 
 // One K tile of split operands into the accumulators: two k steps of 16, each
-// six products of pieces.  m l, l m and l l (at most 2^-26 of x y together) are
-// left out.  h h goes to acc, the five smaller products to low: next to an
-// accumulator that one large term has raised, the matrix instruction drops
-// the last bits of every small term, always the same ones for operands that
-// repeat.  In one accumulator, column sums of (softmax - onehot) W came out
+// six products of pieces.  m l, l m and l l are left out: together at most 2^-24
+// of x y (|m| <= 2^-8, |l| <= 2^-17 of the operand's power of two).  h h
+// goes to acc, the five smaller products to low: next to an accumulator that one
+// large term has raised, the matrix instruction drops the last bits of every
+// small term, always the same ones for operands that repeat.  In one accumulator, column sums of (softmax - onehot) W came out
 // 1.8e-6 off instead of 5.6e-7.
 template <class LA, class LB, int MB, int NB>
 __device__ __forceinline__ void mma_split(floatx16 (&acc)[MB][NB], floatx16 (&low)[MB][NB],
@@ -806,14 +809,15 @@ __device__ __forceinline__ void mma_split(floatx16 (&acc)[MB][NB], floatx16 (&lo
   }
 }
 
-// One fp32 K tile from LDS into the accumulators: four k steps of 8 per
-// half-wave, each a round of LDS reads feeding MB x NB x 4 MFMAs.
-template <int BM, int BN, class LA, class LB, int MB, int NB>
+// One fp32 K tile from LDS into the accumulators: STEPS k steps of 4 per
+// half-wave (the lower half's are k = 0 .. 4 STEPS - 1), each a round of LDS
+// reads feeding MB x NB x 4 MFMAs.
+template <int BM, int BN, class LA, class LB, int STEPS, int MB, int NB>
 __device__ __forceinline__ void mma_ktile(floatx16 (&acc)[MB][NB], const float* A, const float* B,
                                           int wm, int wn, int half, int li) {
   using G = WaveGrid<BM, BN>;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < STEPS; ++j) {
     const int kq = half * 16 + 4 * j;
     float4 a[G::MB], b[G::NB];
 #pragma unroll
@@ -863,8 +867,10 @@ __device__ __forceinline__ void clear(floatx16 (&acc)[MB][NB]) {
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 }
 
-// ROWSUM: rowsum[slice][m] = sum over this slice's k of A[m][k]
-template <int BM, int BN, class LA, class LB, class OM, bool BIAS, bool BATCHED, bool ROWSUM>
+// ROWSUM: rowsum[slice][m] = sum over this slice's k of A[m][k].  FEW: K <= kFewTerms, fp32
+// products only.
+template <int BM, int BN, class LA, class LB, class OM, bool BIAS, bool BATCHED, bool ROWSUM,
+          bool FEW>
 __global__ __launch_bounds__(THREADS, (WaveGrid<BM, BN>::kWaves)) void gemm_kernel(
     LA la, LB lb, float* __restrict__ c, OM om, int64_t slice_stride,
     const float* __restrict__ bias, int64_t M, int64_t N, int64_t K, int64_t k_slice, int tiles_m,
@@ -933,7 +939,27 @@ __global__ __launch_bounds__(THREADS, (WaveGrid<BM, BN>::kWaves)) void gemm_kern
 
   la.fetch(kb, ke, ra);
   lb.fetch(kb, ke, rb);
-  for (int64_t k0 = kb; k0 < ke; k0 += BK) {
+  if constexpr (FEW) {
+    float* const Af = reinterpret_cast<float*>(lds);
+    float* const Bf = Af + LA::kLds;
+    LA::store(Af, ra);
+    LB::store(Bf, rb);
+    if constexpr (ROWSUM) {
+      if (sums) {
+#pragma unroll
+        for (int j = 0; j < LA::kN; ++j) {
+          rs.x += ra[j].x;
+          rs.y += ra[j].y;
+          rs.z += ra[j].z;
+          rs.w += ra[j].w;
+        }
+      }
+    }
+    __syncthreads();
+    mma_ktile<BM, BN, LA, LB, (kFewTerms + 3) / 4>(acc, Af, Bf, wm, wn, half, li);
+    __syncthreads();
+  }
+  for (int64_t k0 = FEW ? ke : kb; k0 < ke; k0 += BK) {
     __syncthreads();   // every wave has read the previous tile
     LA::split_store(As, ra);
     LB::split_store(Bs, rb);
@@ -970,7 +996,8 @@ __global__ __launch_bounds__(THREADS, (WaveGrid<BM, BN>::kWaves)) void gemm_kern
         check = fmaf(acc[a][b][r], 0.f, check);
       }
   float even = li & 1 ? -kSplitUnscale : kSplitUnscale, odd = -even;
-  if (__syncthreads_or(check != 0.f)) {
+  if constexpr (FEW) even = odd = 1.f;
+  if (!FEW && __syncthreads_or(check != 0.f)) {
     even = odd = 1.f;
     clear(acc);
     float* const Af = reinterpret_cast<float*>(lds);
@@ -981,7 +1008,7 @@ __global__ __launch_bounds__(THREADS, (WaveGrid<BM, BN>::kWaves)) void gemm_kern
       LA::store(Af, ra);
       LB::store(Bf, rb);
       __syncthreads();
-      mma_ktile<BM, BN, LA, LB>(acc, Af, Bf, wm, wn, half, li);
+      mma_ktile<BM, BN, LA, LB, 4>(acc, Af, Bf, wm, wn, half, li);
       __syncthreads();
     }
   }
@@ -1004,7 +1031,7 @@ __global__ __launch_bounds__(THREADS, (WaveGrid<BM, BN>::kWaves)) void gemm_kern
 }
 
 template <int BM, int BN, class LA, class LB, class OM, bool BIAS, bool BATCHED = false,
-          bool ROWSUM = false>
+          bool ROWSUM = false, bool FEW = false>
 hipError_t run_gemm(const LA& la, const LB& lb, float* c, OM om, int64_t slice_stride,
                     const float* bias, int64_t M, int64_t N, int64_t K, int64_t slices,
                     hipStream_t s, int64_t batches = 1, Batch bt = Batch{1, 0, 0, 0, 0, 0, 0, 0},
@@ -1015,9 +1042,9 @@ hipError_t run_gemm(const LA& la, const LB& lb, float* c, OM om, int64_t slice_s
     return hipErrorInvalidValue;
   int64_t k_slice = (K + slices - 1) / slices;
   k_slice = (k_slice + BK - 1) / BK * BK;
-  if (ROWSUM != (rowsum != nullptr)) return hipErrorInvalidValue;
+  if (ROWSUM != (rowsum != nullptr) || (FEW && K > kFewTerms)) return hipErrorInvalidValue;
   dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)slices, (unsigned)batches);
-  hipLaunchKernelGGL((gemm_kernel<BM, BN, LA, LB, OM, BIAS, BATCHED, ROWSUM>), grid, dim3(THREADS), 0, s,
+  hipLaunchKernelGGL((gemm_kernel<BM, BN, LA, LB, OM, BIAS, BATCHED, ROWSUM, FEW>), grid, dim3(THREADS), 0, s,
                      la, lb, c, om, slice_stride, bias, M, N, K, k_slice, (int)tiles_m,
                      (int)tiles_n, bt, rowsum);
   return hipGetLastError();
@@ -1069,6 +1096,14 @@ hipError_t dispatch(FA fa, FB fb, float* c, OM om, int64_t slice_stride, const f
                     int64_t M, int64_t N, int64_t K, int64_t slices, hipStream_t s,
                     int64_t batches = 1, Batch bt = Batch{1, 0, 0, 0, 0, 0, 0, 0},
                     float* rowsum = nullptr) {
+  if (K <= kFewTerms) {
+    LAT<64> a{};
+    LBT<64> b{};
+    fa(a);
+    fb(b);
+    return run_gemm<64, 64, LAT<64>, LBT<64>, OM, BIAS, BATCHED, ROWSUM, true>(
+        a, b, c, om, slice_stride, bias, M, N, K, slices, s, batches, bt, rowsum);
+  }
   switch (pick_shape(M, N, K / slices, slices * batches)) {
     case S256x64:
       if constexpr (!BATCHED) {
@@ -1128,11 +1163,13 @@ hipError_t dispatch_dense(FA fa, FB fb, float* c, int64_t ldc, const float* bias
                                                    slices, s, batches, bt, rowsum);
 }
 
-// one explicit tile shape, loaders instantiated at its extents
+// one explicit tile shape, loaders instantiated at its extents (reductions of few terms: dispatch)
 template <int BM, int BN, template <int> class LAT, template <int> class LBT, class FA, class FB,
           class OM>
 hipError_t dispatch_shape(FA fa, FB fb, float* c, OM om, int64_t slice_stride, int64_t M,
                           int64_t N, int64_t K, int64_t slices, hipStream_t s) {
+  if (K <= kFewTerms)
+    return dispatch<LAT, LBT, false>(fa, fb, c, om, slice_stride, nullptr, M, N, K, slices, s);
   LAT<BM> a{};
   LBT<BN> b{};
   fa(a);

@@ -138,6 +138,36 @@ def test_linear_split_range(M, K, N, kind):
     same(dX, refs[2])
 
 
+@pytest.mark.parametrize("terms", [1, 2, 3, 4, 5])
+def test_products_of_few_terms(terms):
+    """Reductions of a handful of terms are no further from float64 than fp32 arithmetic: a single
+    term is the rounded product, bit for bit; n terms stay within n roundings of the sum of their
+    magnitudes.  Forward, input gradient and weight gradient (whose bias gradient takes the same
+    workgroups), tiles with ragged edges, and a 1 x 1 convolution."""
+    n, a, b = terms, f32(133, terms), f32(70, terms)
+    ref, mag = d(a) @ d(b).T, np.abs(d(a)) @ np.abs(d(b)).T
+
+    def check(got, ref, mag):
+        if n == 1:
+            assert np.array_equal(got, ref.astype(np.float32))
+        assert np.all(np.abs(got - ref) <= n * 2.0 ** -24 * mag + 2.0 ** -149)
+
+    Y = run_fn("linear_fwd", [(a, ooc.R), (b, ooc.R), (np.zeros(70, np.float32), ooc.R),
+                              (((133, 70), "f32"), ooc.W)], [133, n, 70])[3]
+    check(Y, ref, mag)
+    dX = run_fn("linear_bwd_x", [(np.ascontiguousarray(b.T), ooc.R), (a, ooc.R),
+                                 (((133, 70), "f32"), ooc.W)], [133, 70, n])[2]
+    check(dX, ref, mag)
+    X, G = np.ascontiguousarray(b.T), np.ascontiguousarray(a.T)
+    dW, db = run_fn("linear_bwd_w", [(X, ooc.R), (G, ooc.R), (((133, 70), "f32"), ooc.W),
+                                     (((133,), "f32"), ooc.W)], [n, 70, 133, 1])[2:4]
+    check(dW, ref, mag)
+    check(db, d(G).sum(0), np.abs(d(G)).sum(0))
+    conv = run_fn("conv_fwd", [(a.reshape(1, 7, 19, n), ooc.R), (b.reshape(70, 1, 1, n), ooc.R),
+                               (((133, 70), "f32"), ooc.W)], [1, 7, 19, n, 70, 1, 1, 1, 0, 7, 19])[2]
+    check(conv, ref, mag)
+
+
 def test_linear_far_rows():
     """Rows of more than 2^21 values: the loaders with 64-bit addresses."""
     M, K, N = 3, (1 << 21) + 5, 2
