@@ -122,18 +122,32 @@ __device__ inline void keep(T& v) {
 // recomputes its tile (see gemm_kernel).  The remainders are single two-term
 // dot products with (-1, 0) and (0, -1): 4.5 vector instructions per value.
 //
-// Odd rows of either operand are negated (scale -2^40) and odd outputs (row +
-// column) negated back.  The matrix instruction aligns its 16 products and the
-// accumulator to the largest and drops what falls below 2^-26 of it towards
-// minus infinity: each result is closer to the exact one than fp32 products
-// give (relative error 4.9e-7 against 5.7e-7 at a reduction of 1024), but the
-// errors share a sign, about 5e-8 of a typical result, and a sum over 8192 rows
-// (a bias or normalisation gradient) came out 5e-6 off instead of 6e-7.  With
-// the signs alternating along both directions it cancels in such sums.
+// The matrix instruction aligns its 16 products and the accumulator to the largest and cuts off
+// what falls below: of the accumulator towards minus infinity, of each product towards zero, at
+// 2^-24 of the largest (seen on single products).  Each result is closer to the exact one than
+// fp32 products give, but such errors share a sign, and sums over many of them show it.
+//
+// The accumulator's: about 5e-8 of a typical result; a sum over 8192 rows (a bias or normalisation
+// gradient) came out 5e-6 off instead of 6e-7.  So odd rows of either operand are negated (scale
+// -2^40) and odd outputs (row + column) negated back: with the signs alternating along both
+// directions it cancels in such sums.
+//
+// The products': h h has 16 bits, so every product below 2^-8 of the largest is cut, and where the
+// terms of a column share a sign (inputs behind a ReLU, gradients that a mask has thinned out) the
+// cuts of a column do too, whatever the outputs' signs: about 5e-10 of a typical result, which in
+// sums over a convolution's pixels outgrows the rounding of fp32 products.  Sums of 200704 products
+// of non-negative rows at K = 64 were off by 2.5e-7 sqrt(rows) of a typical result instead of
+// 1.0e-7, the shift gradient of a batch normalisation behind a 7 x 7 convolution by 7.0e-5 instead
+// of 4.6e-5.  Convolutions therefore give one operand's h only 6 bits (NARROW; h is rounded half
+// away from zero, which leaves remainders of 17 bits and then 8: still exact), so that products
+// have 14: 0.95e-7, 5.6e-5, and gradients of the network's other layers at 0.5 to 1.0 of the error
+// of fp32 products.  Two instructions a value more for that operand: steps of convolution networks
+// 0.98 to 1.01 times as long.  The rows of dense layers are fewer and their sums don't cancel.
 constexpr float kSplitScale = 0x1p40f, kSplitUnscale = 0x1p-80f;
 constexpr int kPieces = 3;
-constexpr int kFewTerms = 4;
+constexpr int kFewTerms = 4;   // at 2 terms 2.6e-8 (with a 6-bit h, below, 3.4e-8) against 3.1e-8, at 4 2.7 (3.4) against 4.0
 
+template <bool NARROW>
 __device__ __forceinline__ void split2(float x, float y, float scale, uint32_t (&o)[kPieces]) {
   // (-1, 0) and (0, -1) as register operands: as constants, the compiler would encode one of them
   // as an inline -1.0, which this instruction does not read as a pair (wrong results measured)
@@ -142,7 +156,14 @@ __device__ __forceinline__ void split2(float x, float y, float scale, uint32_t (
   const bf16x2 first = __builtin_bit_cast(bf16x2, c0), second = __builtin_bit_cast(bf16x2, c1);
   x *= scale;
   y *= scale;
-  const bf16x2 h = __builtin_convertvector((floatx2){x, y}, bf16x2);
+  bf16x2 h;
+  if constexpr (NARROW) {   // rounded half away from zero; an infinity stays one
+    const uint32_t u = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, y) + 0x00020000u,
+                                             __builtin_bit_cast(uint32_t, x) + 0x00020000u, 0x07060302u);
+    h = __builtin_bit_cast(bf16x2, u & 0xfffcfffcu);
+  } else {
+    h = __builtin_convertvector((floatx2){x, y}, bf16x2);
+  }
   x = __builtin_amdgcn_fdot2_f32_bf16(h, first, x, false);
   y = __builtin_amdgcn_fdot2_f32_bf16(h, second, y, false);
   const bf16x2 m = __builtin_convertvector((floatx2){x, y}, bf16x2);
@@ -170,6 +191,7 @@ __device__ inline int rowk_index(int i, int k) { return i * BK + ((((k >> 2) ^ i
 template <int E>
 struct RowK {
   static constexpr bool kRowOfK = true;
+  static constexpr bool kPixels = false;
   static constexpr int kN = E / 32;
   static constexpr int kLds = E * BK;            // floats of the fp32 tile
   static constexpr int kPiece = E * BK * 2;      // bytes of one piece
@@ -181,14 +203,15 @@ struct RowK {
       *reinterpret_cast<float4*>(&lds[rowk_index(row(j), koff())]) = r[j];
   }
   __device__ static int octet(int r, int o) { return r * 64 + (((o ^ (r >> 2)) & 3) << 4); }
+  template <bool NARROW>
   __device__ static void split_store(char* lds, const float4 (&r)[kN]) {
     const int q = threadIdx.x & 7;
     const float scale = row(0) & 1 ? -kSplitScale : kSplitScale;   // the same parity for every j
 #pragma unroll
     for (int j = 0; j < kN; ++j) {
       uint32_t u[kPieces], v[kPieces];
-      split2(r[j].x, r[j].y, scale, u);
-      split2(r[j].z, r[j].w, scale, v);
+      split2<NARROW>(r[j].x, r[j].y, scale, u);
+      split2<NARROW>(r[j].z, r[j].w, scale, v);
       char* d = lds + octet(row(j), q >> 1) + (q & 1) * 8;
 #pragma unroll
       for (int p = 0; p < kPieces; ++p) *reinterpret_cast<uint2*>(d + p * kPiece) = make_uint2(u[p], v[p]);
@@ -201,6 +224,7 @@ struct RowK {
 template <int E>
 struct RowM {
   static constexpr bool kRowOfK = false;
+  static constexpr bool kPixels = false;
   static constexpr int kN = E / 32;
   static constexpr int kItems = E == 192 ? 3 : 1;
   static constexpr int kR = kN / kItems;
@@ -217,6 +241,7 @@ struct RowM {
   __device__ static int octet(int r, int o) {
     return ((r >> 2) + (r & 3) * (E / 4)) * 64 + (((o ^ r ^ (r >> 4)) & 3) << 4);
   }
+  template <bool NARROW>
   __device__ static void split_store(char* lds, const float4 (&r)[kN]) {
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
@@ -227,7 +252,7 @@ struct RowM {
         uint32_t u[(kR + 1) / 2][kPieces];
 #pragma unroll
         for (int j = 0; j < (kR + 1) / 2; ++j)
-          split2(comp(r[i * kR + 2 * j], e), kR > 1 ? comp(r[i * kR + 2 * j + (kR > 1)], e) : 0.f,
+          split2<NARROW>(comp(r[i * kR + 2 * j], e), kR > 1 ? comp(r[i * kR + 2 * j + (kR > 1)], e) : 0.f,
                  e & 1 ? -kSplitScale : kSplitScale, u[j]);
 #pragma unroll
         for (int p = 0; p < kPieces; ++p) {
@@ -325,6 +350,16 @@ struct MatM : RowM<E> {
   }
 };
 
+// The pixel operand of a 1 x 1 convolution, which is a plain matrix
+template <int E>
+struct PixelK : MatK<E> {
+  static constexpr bool kPixels = true;
+};
+template <int E>
+struct PixelM : MatM<E> {
+  static constexpr bool kPixels = true;
+};
+
 // The same two views with 64-bit addresses, for ld > kMaxLd
 template <int E>
 struct MatKFar : RowK<E> {
@@ -396,6 +431,7 @@ __device__ inline int clampi(int v, int lo, int hi) { return min(max(v, lo), hi)
 template <int E, int MODE>
 struct ConvPatch : RowK<E> {
   using Base = RowK<E>;
+  static constexpr bool kPixels = true;
   const float* x;
   int H, W, C, S, st, pad;
   FastDiv dQ, dPQ, dC, dS, dSC;   // by Q, P Q, C, S, S C
@@ -500,6 +536,7 @@ struct ConvPatch : RowK<E> {
 template <int E, int MODE>
 struct ConvGradTap : RowK<E> {
   using Base = RowK<E>;
+  static constexpr bool kPixels = true;
   const float* dy;
   int P, Q, K, nR, nS, a, b;
   FastDiv dWc, dHWc, dK, dnS, dSK;   // by Wc, Hc Wc, K, nS, nS K
@@ -630,6 +667,7 @@ struct ConvFilterTap : RowM<E> {
 template <int E, int MODE>
 struct ConvPixelPatch : RowM<E> {
   using Base = RowM<E>;
+  static constexpr bool kPixels = true;
   using Off = std::conditional_t<MODE == SCALAR, int64_t, int>;
   static constexpr int kPer = MODE == VEC4 ? 1 : 4;   // taps per float4
   static constexpr int kT = kPer * Base::kItems;
@@ -765,7 +803,8 @@ struct WaveGrid {
 
 // One K tile of split operands into the accumulators: two k steps of 16, each
 // six products of pieces.  m l, l m and l l are left out: together at most 2^-24
-// of x y (|m| <= 2^-8, |l| <= 2^-17 of the operand's power of two).  h h
+// of x y (|m| <= 2^-8, |l| <= 2^-17 of the operand's power of two), 5.6e-9 in the
+// root mean square, or 2^-22 and 2.3e-8 where one operand's h is narrow.  h h
 // goes to acc, the five smaller products to low: next to an accumulator that one
 // large term has raised, the matrix instruction drops the last bits of every
 // small term, always the same ones for operands that repeat.  In one accumulator, column sums of (softmax - onehot) W came out
@@ -877,6 +916,7 @@ __global__ __launch_bounds__(THREADS, (WaveGrid<BM, BN>::kWaves)) void gemm_kern
     int tiles_n, Batch bt, float* __restrict__ rowsum) {
   using G = WaveGrid<BM, BN>;
   constexpr int MB = G::MB, NB = G::NB;
+  constexpr bool kNarrow = LA::kPixels || LB::kPixels;
   // Workgroup (tile, slice, batch) from an XCD-aware order: the hardware hands
   // linear workgroup h to XCD h mod 8, so logical ids are laid out so that each
   // XCD (with its own L2) gets one contiguous run of them, and neighbouring
@@ -961,8 +1001,8 @@ __global__ __launch_bounds__(THREADS, (WaveGrid<BM, BN>::kWaves)) void gemm_kern
   }
   for (int64_t k0 = FEW ? ke : kb; k0 < ke; k0 += BK) {
     __syncthreads();   // every wave has read the previous tile
-    LA::split_store(As, ra);
-    LB::split_store(Bs, rb);
+    LA::template split_store<false>(As, ra);
+    LB::template split_store<kNarrow>(Bs, rb);
     if constexpr (ROWSUM) {
       if (sums) {
 #pragma unroll
@@ -1372,8 +1412,8 @@ hipError_t conv_fwd(const float* X, const float* W, float* Y, const ConvShape& c
   const int64_t M = c.N * c.P * c.Q, N = c.K, K = c.R * c.S * c.C;
   if (!fits31(M) || !fits31(K)) return hipErrorInvalidValue;
   if (pointwise(c) && N > 32)   // Y[NPQ][K] = X[NPQ][C] W[K][C]^T
-    return dispatch_dense<MatK, MatK, false>(dense(X, c.C, K), dense(W, c.C, K), Y, N, nullptr, M,
-                                             N, K, 1, s);
+    return dispatch_dense<PixelK, MatK, false>(dense(X, c.C, K), dense(W, c.C, K), Y, N, nullptr, M,
+                                               N, K, 1, s);
   auto fa = [&](auto& a) {
     a.x = X; a.H = (int)c.H; a.W = (int)c.W; a.C = (int)c.C; a.S = (int)c.S;
     a.st = (int)c.stride; a.pad = (int)c.pad;
@@ -1410,8 +1450,8 @@ hipError_t conv_bwd_x(const float* W, const float* dY, float* dX, const ConvShap
   if (c.C % 4 != 0) return hipErrorInvalidValue;   // every conv with an input gradient has C % 4 == 0
   if (!fits31(c.N * c.H * c.W) || !fits31(c.R * c.S * c.K)) return hipErrorInvalidValue;
   if (pointwise(c))   // dX[NHW][C] = dY[NHW][K] W[K][C]
-    return dispatch_dense<MatK, MatM, false>(dense(dY, c.K, c.K), dense(W, c.C, c.K), dX, c.C,
-                                             nullptr, c.N * c.H * c.W, c.C, c.K, 1, s);
+    return dispatch_dense<PixelK, MatM, false>(dense(dY, c.K, c.K), dense(W, c.C, c.K), dX, c.C,
+                                               nullptr, c.N * c.H * c.W, c.C, c.K, 1, s);
   const int64_t st = c.stride;
   // one GEMM per stride class (ph, pw) of input pixels; a class no tap reaches gets zeros
   for (int64_t ph = 0; ph < st; ++ph)
@@ -1486,8 +1526,8 @@ hipError_t conv_bwd_w(const float* X, const float* dY, float* dW, float* part, i
     e = dispatch_shape<64, 192, MatM, ConvPixelPatchV>(fa, fb, out, om, M * N, M, N, K, slices, s);
   else if (pointwise(c))
     // dW[K][C] = dY^T X over the pixel rows: the dense weight gradient's loaders
-    e = dispatch_dense<MatM, MatM, false>(fa, dense(X, c.C, K), out, N, nullptr, M, N, K, slices,
-                                          s);
+    e = dispatch_dense<MatM, PixelM, false>(fa, dense(X, c.C, K), out, N, nullptr, M, N, K, slices,
+                                            s);
   else if (near)
     e = dispatch_dense<MatM, ConvPixelPatchV, false>(fa, fb, out, N, nullptr, M, N, K, slices, s);
   else if (fits)
