@@ -108,11 +108,14 @@ def test_linear(M, K, N, S):
 @pytest.mark.parametrize("M,K,N", [(70, 100, 66), (129, 33, 257), (1, 7, 3)])
 def test_linear_split_range(M, K, N, kind):
     """The products of split operands hold over the whole fp32 range: subnormal inputs (times large
-    ones), sums past 2^48 and infinities or NaN, whose tiles are computed again by fp32 products.
-    Tolerance as for every single kernel, relative to the largest element of the finite ones."""
+    ones, so that results are ordinary), sums past 2^48 and infinities or NaN, whose tiles are
+    computed again by fp32 products.  Tolerance as for every single kernel, relative to the largest
+    element of the finite ones."""
     X, Wt, b, G = f32(M, K), f32(N, K), np.zeros(N, np.float32), f32(M, N)
+    Gw = G                                    # the weight gradient's dY
     if kind == "subnormal":
-        X, Wt, G = X * np.float32(1e-39), Wt * np.float32(1e20), G * np.float32(1e-40)
+        X, Wt, G, Gw = (v * np.float32(c) for v, c in ((X, 1e-39), (Wt, 1e20), (G, 1e-40),
+                                                       (G, 1e20)))
     elif kind == "large":
         X, Wt, G = X * np.float32(1e27), Wt * np.float32(1e9), G * np.float32(1e8)
     elif kind == "special":
@@ -123,16 +126,23 @@ def test_linear_split_range(M, K, N, kind):
         assert np.array_equal(np.isnan(got), np.isnan(ref)), kind
         inf = np.isinf(ref)
         assert np.array_equal(got[inf], ref[inf]), kind
+        assert fine.sum() == 0 or np.abs(ref[fine]).max() > 1e-22, kind   # rel_err's floor is 1e-30
         assert fine.sum() == 0 or rel_err(got[fine], ref[fine]) < TOL, kind
 
     with np.errstate(invalid="ignore"):
-        refs = (d(X) @ d(Wt).T, d(G).T @ d(X), d(G) @ d(Wt))
+        refs = (d(X) @ d(Wt).T, d(Gw).T @ d(X), d(G) @ d(Wt), d(Gw).sum(axis=0))
     (_, _, _, Y) = run_fn("linear_fwd", [(X, ooc.R), (Wt, ooc.R), (b, ooc.R),
                                           (((M, N), "f32"), ooc.W)], [M, K, N])
     same(Y, refs[0])
-    dW = run_fn("linear_bwd_w", [(X, ooc.R), (G, ooc.R), (((N, K), "f32"), ooc.W),
-                                 (((N,), "f32"), ooc.W)], [M, K, N, 1])[2]
+    dW, db = run_fn("linear_bwd_w", [(X, ooc.R), (Gw, ooc.R), (((N, K), "f32"), ooc.W),
+                                     (((N,), "f32"), ooc.W)], [M, K, N, 1])[2:4]
     same(dW, refs[1])
+    same(db, refs[3])
+    if kind == "subnormal":   # and with dY subnormal instead of X
+        big = f32(M, K) * np.float32(1e20)
+        dW = run_fn("linear_bwd_w", [(big, ooc.R), (G, ooc.R), (((N, K), "f32"), ooc.W),
+                                     (((N,), "f32"), ooc.W)], [M, K, N, 1])[2]
+        same(dW, d(G).T @ d(big))
     (_, _, dX) = run_fn("linear_bwd_x", [(Wt, ooc.R), (G, ooc.R), (((M, K), "f32"), ooc.W)],
                         [M, K, N])
     same(dX, refs[2])
