@@ -1070,6 +1070,10 @@ __global__ __launch_bounds__(THREADS, (WaveGrid<BM, BN>::kWaves)) void gemm_kern
                                wn, half, li);
 }
 
+// Tiles of a launch: a grid's threads along x are counted in 32 bits, and a launch of more runs
+// the remainder without an error.
+constexpr int64_t kMaxTiles = (int64_t(1) << 32) / THREADS - 1;
+
 template <int BM, int BN, class LA, class LB, class OM, bool BIAS, bool BATCHED = false,
           bool ROWSUM = false, bool FEW = false>
 hipError_t run_gemm(const LA& la, const LB& lb, float* c, OM om, int64_t slice_stride,
@@ -1077,7 +1081,7 @@ hipError_t run_gemm(const LA& la, const LB& lb, float* c, OM om, int64_t slice_s
                     hipStream_t s, int64_t batches = 1, Batch bt = Batch{1, 0, 0, 0, 0, 0, 0, 0},
                     float* rowsum = nullptr) {
   const int64_t tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  if (tiles_m * tiles_n > INT32_MAX / 2 || slices > 65535 || batches > 65535 || batches < 1 ||
+  if (tiles_m * tiles_n > kMaxTiles || slices > 65535 || batches > 65535 || batches < 1 ||
       tiles_m * tiles_n * slices * batches > INT32_MAX)
     return hipErrorInvalidValue;
   int64_t k_slice = (K + slices - 1) / slices;
@@ -1137,11 +1141,11 @@ hipError_t dispatch(FA fa, FB fb, float* c, OM om, int64_t slice_stride, const f
                     int64_t batches = 1, Batch bt = Batch{1, 0, 0, 0, 0, 0, 0, 0},
                     float* rowsum = nullptr) {
   if (K <= kFewTerms) {
-    LAT<64> a{};
+    LAT<128> a{};
     LBT<64> b{};
     fa(a);
     fb(b);
-    return run_gemm<64, 64, LAT<64>, LBT<64>, OM, BIAS, BATCHED, ROWSUM, true>(
+    return run_gemm<128, 64, LAT<128>, LBT<64>, OM, BIAS, BATCHED, ROWSUM, true>(
         a, b, c, om, slice_stride, bias, M, N, K, slices, s, batches, bt, rowsum);
   }
   switch (pick_shape(M, N, K / slices, slices * batches)) {
@@ -1201,6 +1205,23 @@ hipError_t dispatch_dense(FA fa, FB fb, float* c, int64_t ldc, const float* bias
                           float* rowsum = nullptr) {
   return dispatch<LAT, LBT, BIAS, BATCHED, ROWSUM>(fa, fb, c, DenseOut{ldc}, M * ldc, bias, M, N, K,
                                                    slices, s, batches, bt, rowsum);
+}
+
+// A product whose rows are those of plain matrices, in launches of as many rows as one takes: at
+// most kMaxTiles of the smallest tiles, 64 x 64.  (Convolutions have fewer than 2^31 pixels, and at
+// most 64 columns where these fill memory: fewer than 2^24 tiles of 128 x 64.)
+template <template <int> class LAT, template <int> class LBT, bool BIAS, class FB>
+hipError_t dispatch_rows(const float* A, FB fb, float* c, const float* bias, int64_t M, int64_t N,
+                         int64_t K, hipStream_t s) {
+  const int64_t cols = (N + 63) / 64;
+  const int64_t rows = std::max<int64_t>(1, kMaxTiles / cols / 4) * 256;   // whole tiles of any shape
+  for (int64_t m = 0; m < M; m += rows) {
+    const auto fa = [=](auto& l) { l.p = A + m * K; l.ld = K; l.kdim = K; };
+    const hipError_t e = dispatch_dense<LAT, LBT, BIAS>(fa, fb, c + m * N, N, bias,
+                                                        std::min(rows, M - m), N, K, 1, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // one explicit tile shape, loaders instantiated at its extents (reductions of few terms: dispatch)
@@ -1343,18 +1364,18 @@ bool window_fits(int64_t pixels, int64_t rows, int64_t cols, int64_t st, int64_t
 
 hipError_t linear_fwd(const float* X, const float* W, const float* b, float* Y, int64_t M,
                       int64_t K, int64_t N, hipStream_t s) {
-  const auto fa = dense(X, K, K), fb = dense(W, K, K);
-  if (K <= kMaxLd) return dispatch_dense<MatK, MatK, true>(fa, fb, Y, N, b, M, N, K, 1, s);
-  return dispatch_dense<MatKFar, MatKFar, true>(fa, fb, Y, N, b, M, N, K, 1, s);
+  const auto fb = dense(W, K, K);
+  if (K <= kMaxLd) return dispatch_rows<MatK, MatK, true>(X, fb, Y, b, M, N, K, s);
+  return dispatch_rows<MatKFar, MatKFar, true>(X, fb, Y, b, M, N, K, s);
 }
 
 hipError_t linear_bwd_x(const float* W, const float* dY, float* dX, int64_t M, int64_t K,
                         int64_t N, hipStream_t s) {
   // dX[M][K] = dY[M][N] W[N][K]: A = dY (contiguous along the reduction), B[n_out][k_in] = W
-  const auto fa = dense(dY, N, N), fb = dense(W, K, N);
+  const auto fb = dense(W, K, N);
   if (std::max(N, K) <= kMaxLd)
-    return dispatch_dense<MatK, MatM, false>(fa, fb, dX, K, nullptr, M, K, N, 1, s);
-  return dispatch_dense<MatKFar, MatMFar, false>(fa, fb, dX, K, nullptr, M, K, N, 1, s);
+    return dispatch_rows<MatK, MatM, false>(dY, fb, dX, nullptr, M, K, N, s);
+  return dispatch_rows<MatKFar, MatMFar, false>(dY, fb, dX, nullptr, M, K, N, s);
 }
 
 hipError_t linear_bwd_w(const float* X, const float* dY, float* dW, float* db, float* part,

@@ -636,3 +636,36 @@ def test_full_size_function_matches_oracle(cid, op, attrs, sig):
     rep = Report(cid)
     CHECKS[op](op, attrs, sig, rep, np.random.default_rng(zlib.crc32(cid.encode())))
     print(f"{cid}: worst error / bound {rep.worst:.3f}", flush=True)
+
+
+def test_dense_layer_of_more_rows_than_a_launch_takes():
+    """2^31 + 129 rows, more tiles than the 32-bit count of a launch's threads holds: forward and
+    input gradient of a layer of one input and one output, exact up to the rounding of x w + b."""
+    M, step = (1 << 31) + 129, 1 << 27
+    w, b = np.float32(-2.0), np.float32(-0.3)
+    ctx = ooc.Context(0)
+    try:
+        x, y, dx = (ctx.add_var(M * 4, k) for k in (ooc.INPUT, ooc.OUTPUT, ooc.OUTPUT))
+        wv, bv = ctx.add_var(4, ooc.INPUT), ctx.add_var(4, ooc.INPUT)
+        ctx.add_fn("linear_fwd", [x, wv, bv, y], [ooc.R, ooc.R, ooc.R, ooc.W], [M, 1, 1])
+        ctx.add_fn("linear_bwd_x", [wv, x, dx], [ooc.R, ooc.R, ooc.W], [M, 1, 1])
+        ctx.set_chunk(64 << 20)
+        ctx.build_schedule()
+        ctx.prepare()
+        ctx.host_view(wv, np.float32)[0], ctx.host_view(bv, np.float32)[0] = w, b
+        pattern = synth.normal_pool(step, seed=5)
+        for i in range(0, M, step):
+            xs = ctx.host_view(x, np.float32)[i:i + step]
+            xs[...] = pattern[:xs.size] + np.float32(i >> 27)
+        print("inputs made", flush=True)
+        ctx.upload()
+        ctx.step(0.0, 0.0)
+        ctx.download()
+        print("step done", flush=True)
+        for i in range(0, M, step):
+            xs, ys, ds = (ctx.host_view(v, np.float32)[i:i + step] for v in (x, y, dx))
+            prod = xs * w
+            assert np.array_equal(ds, prod), i
+            assert np.array_equal(ys, prod + b), i
+    finally:
+        ctx.close()
