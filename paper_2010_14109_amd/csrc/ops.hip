@@ -980,23 +980,29 @@ hipError_t sgd(int count, float* const* w, const float* const* g, float* const* 
 
 hipError_t softmax_ce(const float* logits, const int32_t* labels, float* loss, float* dlogits,
                       int64_t N, int64_t classes, hipStream_t s) {
-  // up to 32 values a lane; past 32 x 1024 the row no longer fits a workgroup's registers
+  // up to 32 values a lane; past 32 x 1024 the row no longer fits a workgroup's registers.  A
+  // launch's threads are counted in 32 bits: more rows than that holds of a kernel's groups take
+  // the 64 lanes of softmax_ce_rows too.
   auto rows = [&](auto kernel, int group) {
     const int threads = std::max(group, TPB), per = threads / group;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((N + per - 1) / per)), dim3(threads), 0, s, logits,
-                       labels, loss, dlogits, N, classes);
+    const int64_t blocks = (N + per - 1) / per;
+    if (blocks * threads >= int64_t(1) << 32) return false;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, s, logits, labels, loss,
+                       dlogits, N, classes);
+    return true;
   };
-  if (classes <= 8) rows(softmax_ce_regs<8, 1>, 8);
-  else if (classes <= 16) rows(softmax_ce_regs<16, 1>, 16);
-  else if (classes <= 32) rows(softmax_ce_regs<32, 1>, 32);
-  else if (classes <= 64) rows(softmax_ce_regs<64, 1>, 64);
-  else if (classes <= 256) rows(softmax_ce_regs<64, 4>, 64);
-  else if (classes <= 1024) rows(softmax_ce_regs<64, 16>, 64);
-  else if (classes <= 4096) rows(softmax_ce_regs<256, 16>, 256);
-  else if (classes <= 8192) rows(softmax_ce_regs<256, 32>, 256);
-  else if (classes <= 16384) rows(softmax_ce_regs<512, 32>, 512);
-  else if (classes <= 32768) rows(softmax_ce_regs<1024, 32>, 1024);
-  else rows(softmax_ce_rows, 64);
+  const bool held = classes <= 8      ? rows(softmax_ce_regs<8, 1>, 8)
+                    : classes <= 16    ? rows(softmax_ce_regs<16, 1>, 16)
+                    : classes <= 32    ? rows(softmax_ce_regs<32, 1>, 32)
+                    : classes <= 64    ? rows(softmax_ce_regs<64, 1>, 64)
+                    : classes <= 256   ? rows(softmax_ce_regs<64, 4>, 64)
+                    : classes <= 1024  ? rows(softmax_ce_regs<64, 16>, 64)
+                    : classes <= 4096  ? rows(softmax_ce_regs<256, 16>, 256)
+                    : classes <= 8192  ? rows(softmax_ce_regs<256, 32>, 256)
+                    : classes <= 16384 ? rows(softmax_ce_regs<512, 32>, 512)
+                    : classes <= 32768 ? rows(softmax_ce_regs<1024, 32>, 1024)
+                                       : false;
+  if (!held && !rows(softmax_ce_rows, 64)) return hipErrorInvalidConfiguration;
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(mean_rows, dim3(1), dim3(MEAN_T), 0, s, loss, N, aligned16(loss));

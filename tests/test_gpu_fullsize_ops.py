@@ -669,3 +669,45 @@ def test_dense_layer_of_more_rows_than_a_launch_takes():
             assert np.array_equal(ys, prod + b), i
     finally:
         ctx.close()
+
+
+def test_softmax_ce_of_more_rows_than_a_launch_of_workgroups_takes():
+    """2^24 rows of 1025 classes (a workgroup per row would be 2^32 threads): logits x w + b made
+    and their gradients reduced by dense layers of one input, losses and input gradients of 4096
+    rows against float64.  The gradients sum 1025 terms p w / N with one factor each of rounding,
+    exponential and division, 8 u of the magnitudes in all, and their sum's sqrt(T) u."""
+    N, C = 1 << 24, 1025
+    w, b = (synth.normal_pool(C, seed=s) for s in (6, 7))
+    ctx = ooc.Context(0)
+    try:
+        x, z, wv, bv = (ctx.add_var(n * 4, k) for n, k in ((N, ooc.INPUT), (N * C, ooc.TEMP),
+                                                           (C, ooc.INPUT), (C, ooc.INPUT)))
+        lab, loss = ctx.add_var(N * 4, ooc.INPUT), ctx.add_var((N + 1) * 4, ooc.OUTPUT)
+        dz, dx = ctx.add_var(N * C * 4, ooc.TEMP), ctx.add_var(N * 4, ooc.OUTPUT)
+        ctx.add_fn("linear_fwd", [x, wv, bv, z], [ooc.R, ooc.R, ooc.R, ooc.W], [N, 1, C])
+        ctx.add_fn("softmax_ce", [z, lab, loss, dz], [ooc.R, ooc.R, ooc.W, ooc.W], [N, C])
+        ctx.add_fn("linear_bwd_x", [wv, dz, dx], [ooc.R, ooc.R, ooc.W], [N, 1, C])
+        ctx.set_chunk(256 << 20)
+        ctx.build_schedule()
+        ctx.prepare()
+        print("prepared", flush=True)
+        ctx.host_view(wv, np.float32)[...], ctx.host_view(bv, np.float32)[...] = w, b
+        xs, ls = ctx.host_view(x, np.float32), ctx.host_view(lab, np.int32)
+        xs[...] = synth.normal_pool(N, seed=8)
+        ls[...] = np.arange(N, dtype=np.int64) * 7919 % C
+        ctx.upload()
+        ctx.step(0.0, 0.0)
+        ctx.download()
+        print("step done", flush=True)
+        at = np.unique(np.r_[0, N - 1, np.random.default_rng(1).integers(0, N, 4096)])
+        zs = (xs[at, None] * w + b).astype(np.float64)     # one product and one sum, as on the device
+        rows, _, d = ops.softmax_ce(zs, ls[at])
+        d *= at.size / N
+        got = ctx.host_view(loss, np.float32)
+        assert np.abs(got[at] - rows).max() <= 8 * U * (np.abs(rows).max() + np.abs(zs).max())
+        dxs, mag = d @ w.astype(np.float64), np.abs(d) @ np.abs(w)
+        err = np.abs(ctx.host_view(dx, np.float32)[at] - dxs)
+        assert np.all(err <= (math.sqrt(C) + 8 + 2 * np.abs(zs).max()) * U * mag)
+        assert abs(got[N] - got[:N].mean(dtype=np.float64)) <= 1e-5 * abs(got[N])
+    finally:
+        ctx.close()
