@@ -127,12 +127,14 @@ __global__ void sgd_kernel(SgdSet set, float lr, float mu) {
 }
 
 // ---------------------------------------------------------------- many copies
-// Up to kCopySet buffers between device memory and pinned host memory in one
-// launch; a workgroup moves kCopyBlock bytes of the buffer whose block range
-// holds it.  Bound by the host link; a copy call of its own costs about 15 us
+// Up to kCopySet buffers (or pieces of one) between device memory and pinned
+// host memory in one launch; a workgroup moves kCopyBlock bytes of the buffer
+// whose block range holds it.  Bound by the host link; a copy call of its own costs about 15 us
 // however small, and a network has hundreds of variables of a few KiB.
 constexpr int kCopySet = 64;
 constexpr uint32_t kCopyBlock = 16384;
+constexpr uint64_t kCopyBlocks = 1 << 23;   // of a launch at most: 128 GiB
+static_assert(kCopyBlocks * TPB < uint64_t(1) << 32, "a launch's threads are counted in 32 bits");
 struct CopySet {
   char* dst[kCopySet];
   const char* src[kCopySet];
@@ -932,24 +934,30 @@ hipError_t add(const float* a, const float* b, float* y, int64_t n, hipStream_t 
 
 hipError_t copy_many(int count, void* const* dst, const void* const* src, const uint64_t* bytes,
                      hipStream_t s) {
-  for (int k0 = 0; k0 < count; k0 += kCopySet) {
-    CopySet set{};
-    set.n = std::min(kCopySet, count - k0);
-    uint64_t blocks = 0;
-    for (int k = 0; k < set.n; ++k) {
-      set.dst[k] = static_cast<char*>(dst[k0 + k]);
-      set.src[k] = static_cast<const char*>(src[k0 + k]);
-      set.bytes[k] = bytes[k0 + k];
-      set.first[k] = (uint32_t)blocks;
-      blocks += (bytes[k0 + k] + kCopyBlock - 1) / kCopyBlock;
-      if (blocks > INT32_MAX) return hipErrorInvalidValue;
-    }
+  CopySet set{};
+  uint64_t blocks = 0;
+  auto launch = [&] {
     set.first[set.n] = (uint32_t)blocks;
     hipLaunchKernelGGL(copy_kernel, dim3((unsigned)blocks), dim3(TPB), 0, s, set);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+    set.n = 0;
+    blocks = 0;
+    return hipGetLastError();
+  };
+  for (int k = 0; k < count; ++k)
+    for (uint64_t at = 0; at < bytes[k];) {
+      if (set.n == kCopySet || blocks == kCopyBlocks) {
+        const hipError_t e = launch();
+        if (e != hipSuccess) return e;
+      }
+      const uint64_t piece = std::min(bytes[k] - at, (kCopyBlocks - blocks) * kCopyBlock);
+      set.dst[set.n] = static_cast<char*>(dst[k]) + at;
+      set.src[set.n] = static_cast<const char*>(src[k]) + at;
+      set.bytes[set.n] = piece;
+      set.first[set.n++] = (uint32_t)blocks;
+      blocks += (piece + kCopyBlock - 1) / kCopyBlock;
+      at += piece;
+    }
+  return set.n ? launch() : hipSuccess;
 }
 hipError_t accumulate(float* a, const float* b, int64_t n, hipStream_t s) {
   const bool vec = aligned16(a) && aligned16(b);
