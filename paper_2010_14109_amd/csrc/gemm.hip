@@ -81,10 +81,10 @@ __device__ inline float4 zero4() { return make_float4(0.f, 0.f, 0.f, 0.f); }
 // select per load this saves 20 to 40 registers a lane, and rows that are not
 // multiples of 4 need no scalar loads (1379 x 765 x 3067: 0.120 ms with them,
 // 0.060 without).  Rows and columns past M or N that are in bounds read their
-// neighbours: they only reach C entries that are never stored.  The general views (matrices with rows of more than kMaxLd values,
-// channel counts that are not multiples of 4, images too large for 32-bit
-// offsets) form 64-bit addresses per value; their masked lanes load from a
-// block of zeros.
+// neighbours: they only reach C entries that are never stored.  The general views
+// (matrices with rows of more than kMaxLd values, images too large for 32-bit
+// offsets, gradient taps of channel counts that are not multiples of 4) form
+// 64-bit addresses per value; their masked lanes load from a block of zeros.
 constexpr uint32_t kNone = 0x80000000u;   // past the length of every descriptor
 constexpr int64_t kMaxLd = int64_t(1) << 21;   // 255 rows of it stay below 2^31 bytes
 
@@ -1175,16 +1175,14 @@ hipError_t dispatch(FA fa, FB fb, float* c, OM om, int64_t slice_stride, const f
       return run_gemm<64, 128, LAT<64>, LBT<128>, OM, BIAS, BATCHED, ROWSUM>(
           a, b, c, om, slice_stride, bias, M, N, K, slices, s, batches, bt, rowsum);
     }
-    case S64x64:
-      if constexpr (true) {
-        LAT<64> a{};
-        LBT<64> b{};
-        fa(a);
-        fb(b);
-        return run_gemm<64, 64, LAT<64>, LBT<64>, OM, BIAS, BATCHED, ROWSUM>(
-            a, b, c, om, slice_stride, bias, M, N, K, slices, s, batches, bt, rowsum);
-      }
-      [[fallthrough]];
+    case S64x64: {
+      LAT<64> a{};
+      LBT<64> b{};
+      fa(a);
+      fb(b);
+      return run_gemm<64, 64, LAT<64>, LBT<64>, OM, BIAS, BATCHED, ROWSUM>(
+          a, b, c, om, slice_stride, bias, M, N, K, slices, s, batches, bt, rowsum);
+    }
     default: {
       LAT<128> a{};
       LBT<128> b{};
@@ -1256,21 +1254,19 @@ template <int E> using ConvPixelPatchS = ConvPixelPatch<E, SCALAR>;
 bool fits31(int64_t v) { return v >= 0 && v < (int64_t(1) << 31) - 512; }
 
 // Tile of a filter gradient (M = output channels, N = RSC), first rule that
-// applies; the lowering's split-K slice count follows the same rule:
+// applies:
 //   32 x 256 for M <= 32 (no empty tile rows; 32 columns of one tap a thread
 //            when C % 32 == 0);
 //   64 x 192 for M <= 64 when that leaves fewer padded RSC columns than
 //            64 x 128 (RSC = 576 for a 3 x 3 x 64 filter: 3 full tiles, not 4.5);
-//   64 x 64  for M <= 64 and RSC <= 64 (1 x 1 filters, 3-channel inputs);
 //   otherwise the general shapes.
-// The first three need M % 4 == 0 (and C % 4 == 0 for the first two).
-enum class WgradTile { k32x256, k64x192, k64x64, kGeneral };
+// Both only for M and C that are multiples of 4, those they were measured with.
+enum class WgradTile { k32x256, k64x192, kGeneral };
 WgradTile wgrad_tile(int64_t M, int64_t N, int64_t C) {
-  if (M % 4 != 0) return WgradTile::kGeneral;
-  if (M <= 32 && C % 4 == 0) return WgradTile::k32x256;
+  if (M % 4 != 0 || C % 4 != 0) return WgradTile::kGeneral;
+  if (M <= 32) return WgradTile::k32x256;
   const int64_t pad128 = (N + 127) / 128 * 128 - N, pad192 = (N + 191) / 192 * 192 - N;
-  if (M <= 64 && C % 4 == 0 && pad192 < pad128) return WgradTile::k64x192;
-  if (M <= 64 && N <= 64) return WgradTile::k64x64;
+  if (M <= 64 && pad192 < pad128) return WgradTile::k64x192;
   return WgradTile::kGeneral;
 }
 
@@ -1563,14 +1559,23 @@ hipError_t conv_bwd_w(const float* X, const float* dY, float* dW, float* part, i
 }
 
 // Split-K slice count of a weight gradient with M x N outputs reduced over K
-// rows (C = input channels of a filter gradient, -1 for a dense layer).  The
-// launchers above run tiles x s workgroups; a CU holds kResident of them at
-// once (LDS bounds it: 2 for 128 x 128, 64 x 192 and 32 x 256 tiles, 3 for the
-// general 64-wide ones, 4-5 for the 64 x 64 tiles), so a launch
-// takes ceil(tiles s / slots) rounds of K / s rows.  s minimises rounds / s
-// (a partly filled last round leaves most CUs idle behind a few), with at most
-// four rounds and at least 256 rows a slice; the smallest s within 1 % of the
-// best is taken, since every slice adds one partial dW to write and read back.
+// rows (C = input channels of a filter gradient, -1 for a dense layer).  With T
+// tiles of which a CU holds R at once, a launch of T s workgroups takes
+// ceil(T s / (256 R)) rounds of K / s rows.  s minimises rounds / s (a partly
+// filled last round leaves most CUs idle behind a few), with at most four rounds
+// and at least 256 rows a slice; the smallest s within 1 % of the best is taken,
+// since every slice adds one partial dW to write and read back.
+//
+// The count belongs to a network's registered sequence, whose partial sums it
+// sizes.  T and R are those of a rule on sizes alone, stated here; which tile runs
+// is pick_shape's choice for the count that is registered (any tile runs with any
+// count), and it is often a smaller one.  Over the 175 weight gradients of the
+// timed networks and ten drawn ones, each timed with up to 25 counts: within 5 %
+// of the best count in 108, the sum of all 1.5 % over that of the best; worst are
+// small ones, whose 256 rows a slice are too many (3 x 3 20 -> 20 over 931 pixels:
+// 22.9 us with 4 slices, 15.4 with 8), and 64 x 64 outputs, whose count is for 5
+// workgroups a CU (1 x 1 64 -> 64 over 200704 pixels: 34.6 us with 777, 27.7 with
+// 512).
 int64_t wgrad_slices(int64_t M, int64_t N, int64_t K, int64_t C) {
   constexpr int64_t kCUs = 256, kFewTiles = 128, kFewTilesMaxK = 4096;
   int64_t tiles, resident;
@@ -1579,7 +1584,7 @@ int64_t wgrad_slices(int64_t M, int64_t N, int64_t K, int64_t C) {
     tiles = (N + 255) / 256, resident = 2;
   } else if (t == WgradTile::k64x192) {
     tiles = (N + 191) / 192, resident = 2;
-  } else if (t == WgradTile::k64x64) {
+  } else if (C >= 0 && M % 4 == 0 && M <= 64 && N <= 64) {
     tiles = 1, resident = C % 4 == 0 ? 5 : 4;
   } else {
     const int64_t large = ((M + 127) / 128) * ((N + 127) / 128);

@@ -565,7 +565,8 @@ hipError_t bn_reduce(const float* x, float* stats, float* dgamma, float* dbeta, 
 // forward (mode 0): y = (x - mean) invstd gamma + beta, with a ReLU behind it in mode 2; backward
 // (mode 1): dx = gamma invstd (dy - dbeta / rows - xhat dgamma / rows).  Bound by HBM.  vec: four
 // channels a lane (C % 4 == 0, 16-byte aligned arrays); the lane's channel moves by the grid's
-// stride modulo C, so that only the first one takes a division (205 MB: APPLY_FIGS).
+// stride modulo C, so that only the first one takes a division (at 205 MB 76 us against
+// 77 with a division per value: bound by memory either way).
 template <int MODE>
 __global__ void bn_apply(const float* __restrict__ x, const float* __restrict__ dy,
                          const float* __restrict__ stats, const float* __restrict__ gamma,
