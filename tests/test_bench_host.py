@@ -118,3 +118,13 @@ def test_paper_figure_only_for_the_exact_table_1_setting():
     assert bench.paper_figure("resnet50_b1440", 1440, f, "adaptive", "bestfit", "oldest") is None
     assert bench.paper_figure("resnet50_b1440", 1440, f, "adaptive", "pool", "furthest") is None
     assert bench.paper_figure("resnet50_b256", 256, 0.25, "adaptive", "pool", "oldest") is None
+
+
+def test_roofline_peak_is_that_of_the_instructions_that_run():
+    """fp32 products run as six bf16 products: their roof is a sixth of the bf16 peak, above the
+    180 TFLOP/s that large products reach and the 157 of fp32 matrix instructions."""
+    r = bench.roofline({"unit": "flop", "rate": 180.0})
+    assert r["bound"] == "mfma" and r["peak"] == round(2500 / 6, 1) and "bf16" in r["peak_of"]
+    assert r["frac"] == round(180 * 6 / 2500, 4) < 1
+    r = bench.roofline({"unit": "byte", "rate": 4000.0})
+    assert r["bound"] == "hbm" and r["frac"] == 0.5
