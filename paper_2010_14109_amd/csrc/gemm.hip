@@ -1100,7 +1100,12 @@ hipError_t run_gemm(const LA& la, const LB& lb, float* c, OM om, int64_t slice_s
 // of what two 128 x 128 tiles reach together, so smaller tiles only pay where
 // the large ones leave CUs idle or alone.  Rates measured on convolutions and
 // dense products from 32 x 256 x 256 to 12288 x 4096 x 1024, each run with
-// every shape.
+// every shape.  Of 25 such products the rule's shape is within 2 % of the best
+// in 23 (56 x 56 1 x 1 256 -> 128 at batch 64: 117 us on 64 x 64 tiles, 107 on
+// 128 x 64); us with 128 x 128, 128 x 64 and 64 x 64 tiles:
+//   256 x 1024 x 1024     66   45   30      12288 x 1024 x 4096  676  746  806
+//   1379 x 765 x 3067     78   69   64      7 x 7 3 x 3 512, batch 64  264  188  167
+//   8192 x 512 x 1536    101  100  102      28 x 28 3 x 3 128, batch 64  112  137  133
 enum Shape { S128x128, S128x64, S64x128, S256x64, S64x64 };
 struct ShapeRate {
   int bm, bn, resident;
