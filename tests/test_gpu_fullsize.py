@@ -74,6 +74,21 @@ def test_resnet50_against_oracle(batch, hw):
     derived_check(spec, x, labels, params, loss, outs, chunk)
 
 
+@pytest.mark.parametrize("spec", [
+    synth.mlp(batch=131, width=515, depth=5, classes=67),
+    synth.plain_cnn(batch=24, channels=36, depth=5, hw=23),
+    synth.resnet(batch=6, hw=99, width=24, blocks=(1, 1, 1, 1)),
+    synth.densenet(batch=9, hw=32, growth=16, blocks=(3, 3, 3, 3)),
+    synth.unet(batch=2, hw=56, base=20, depth=3)], ids=lambda s: s["name"])
+def test_networks_of_every_kind_under_own_choices(spec):
+    """Every network with ReLUs at a ragged middle size, in core: gradients to rounding instead of
+    to the size of a flipped choice."""
+    x, labels = synth.make_inputs(spec, 0)
+    params = synth.make_params(spec, 1)
+    loss, outs, _ = run_net(spec, x, labels, params)
+    derived_check(spec, x, labels, params, loss, outs, 2 << 20)
+
+
 def test_resnet50_batch256_bench_config_matches_incore():
     spec, chunk, plan = bench_config("resnet50_b256")
     x, labels = synth.make_inputs(spec, 0)
