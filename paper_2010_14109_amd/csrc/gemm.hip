@@ -158,14 +158,16 @@ __device__ __forceinline__ void split2(float x, float y, float scale, uint32_t (
   y *= scale;
   bf16x2 h;
   if constexpr (NARROW) {   // rounded half away from zero; an infinity stays one
-    const uint32_t u = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, y) + 0x00020000u,
-                                             __builtin_bit_cast(uint32_t, x) + 0x00020000u, 0x07060302u);
-    h = __builtin_bit_cast(bf16x2, u & 0xfffcfffcu);
+    const uint32_t hx = (__builtin_bit_cast(uint32_t, x) + 0x00020000u) & 0xfffc0000u;
+    const uint32_t hy = (__builtin_bit_cast(uint32_t, y) + 0x00020000u) & 0xfffc0000u;
+    h = __builtin_bit_cast(bf16x2, __builtin_amdgcn_perm(hy, hx, 0x07060302u));
+    x -= __builtin_bit_cast(float, hx);
+    y -= __builtin_bit_cast(float, hy);
   } else {
     h = __builtin_convertvector((floatx2){x, y}, bf16x2);
+    x = __builtin_amdgcn_fdot2_f32_bf16(h, first, x, false);
+    y = __builtin_amdgcn_fdot2_f32_bf16(h, second, y, false);
   }
-  x = __builtin_amdgcn_fdot2_f32_bf16(h, first, x, false);
-  y = __builtin_amdgcn_fdot2_f32_bf16(h, second, y, false);
   const bf16x2 m = __builtin_convertvector((floatx2){x, y}, bf16x2);
   x = __builtin_amdgcn_fdot2_f32_bf16(m, first, x, false);
   y = __builtin_amdgcn_fdot2_f32_bf16(m, second, y, false);
