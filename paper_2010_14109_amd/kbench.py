@@ -113,13 +113,16 @@ def run(spec, reps=20):
 
 def _counters(d, calls=None):
     """{kernel: {counter: value per call}} of the rocprofv3 csv files under d: the sum over
-    the kernel's dispatches / calls, or the mean per dispatch when calls is None."""
+    the kernel's dispatches / calls, or the mean per dispatch when calls is None.  The upload's
+    copy kernel is not the function's and is left out."""
     acc = defaultdict(lambda: defaultdict(list))
     for f in glob.glob(os.path.join(d, "**", "*_counter_collection.csv"), recursive=True):
         with open(f) as fh:
             for r in csv.DictReader(fh):
                 name = r["Kernel_Name"].replace("ooc::(anonymous namespace)::", "")
                 name = name.replace("void ", "").split("(")[0]
+                if name == "copy_kernel":
+                    continue
                 acc[name][r["Counter_Name"]].append(float(r["Counter_Value"]))
     return {k: {c: sum(x) / (calls or len(x)) for c, x in v.items()} for k, v in acc.items()}
 

@@ -112,3 +112,19 @@ def test_traffic_adds_every_dispatch_of_a_call(tmp_path):
     # without the call count every kernel counts once per call (the mean per dispatch)
     res1, _, _ = kbench.traffic(str(tmp_path / "f"), str(tmp_path / "w"), str(cal))
     assert res1["gemm_kernel<1>"] == pytest.approx((100 * 1024 * 2.0, 10 * 1024 * 1.0))
+
+
+def test_traffic_leaves_the_upload_out(tmp_path):
+    """The harness uploads the inputs with a kernel before the first call: its bytes are not the
+    function's."""
+    for d, counter in (("f", "FETCH_SIZE"), ("w", "WRITE_SIZE")):
+        _counter_csv(str(tmp_path / d), [
+            (1, "ooc::(anonymous namespace)::copy_kernel(ooc::(anonymous namespace)::CopySet)", counter, 5e6),
+            (2, "void ooc::(anonymous namespace)::ew_kernel<0>(x)", counter, 100.0)])
+    assert list(kbench._counters(str(tmp_path / "f"))) == ["ew_kernel<0>"]
+    cal = tmp_path / "cal"
+    for d, counter in (("fetch", "FETCH_SIZE"), ("write", "WRITE_SIZE")):
+        _counter_csv(str(cal / d), [(1, "void ooc::(anonymous namespace)::ew_kernel<0>(x)", counter,
+                                     kbench.CAL_N * 4 / 1024)])
+    res, _, _ = kbench.traffic(str(tmp_path / "f"), str(tmp_path / "w"), str(cal), calls=1)
+    assert res == {"ew_kernel<0>": pytest.approx((102400.0, 102400.0))}
