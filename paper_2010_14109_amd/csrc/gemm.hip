@@ -919,6 +919,7 @@ __global__ __launch_bounds__(THREADS, (WaveGrid<BM, BN>::kWaves)) void gemm_kern
   using G = WaveGrid<BM, BN>;
   constexpr int MB = G::MB, NB = G::NB;
   constexpr bool kNarrow = LA::kPixels || LB::kPixels;
+  constexpr bool kNarrowA = kNarrow && LA::kN < LB::kN;   // the side with fewer values to split
   // Workgroup (tile, slice, batch) from an XCD-aware order: the hardware hands
   // linear workgroup h to XCD h mod 8, so logical ids are laid out so that each
   // XCD (with its own L2) gets one contiguous run of them, and neighbouring
@@ -1003,8 +1004,8 @@ __global__ __launch_bounds__(THREADS, (WaveGrid<BM, BN>::kWaves)) void gemm_kern
   }
   for (int64_t k0 = FEW ? ke : kb; k0 < ke; k0 += BK) {
     __syncthreads();   // every wave has read the previous tile
-    LA::template split_store<false>(As, ra);
-    LB::template split_store<kNarrow>(Bs, rb);
+    LA::template split_store<kNarrowA>(As, ra);
+    LB::template split_store<kNarrow && !kNarrowA>(Bs, rb);
     if constexpr (ROWSUM) {
       if (sums) {
 #pragma unroll

@@ -78,7 +78,7 @@ def test_resnet50_against_oracle(batch, hw):
     synth.mlp(batch=131, width=515, depth=5, classes=67),
     synth.plain_cnn(batch=24, channels=36, depth=5, hw=23),
     synth.resnet(batch=6, hw=99, width=24, blocks=(1, 1, 1, 1)),
-    synth.densenet(batch=9, hw=32, growth=16, blocks=(3, 3, 3, 3)),
+    synth.densenet(batch=9, hw=32, growth=8, blocks=(4, 4, 4, 4)),
     synth.unet(batch=2, hw=56, base=20, depth=3)], ids=lambda s: s["name"])
 def test_networks_of_every_kind_under_own_choices(spec):
     """Every network with ReLUs at a ragged middle size, in core: gradients to rounding instead of
