@@ -145,7 +145,9 @@ __device__ inline void keep(T& v) {
 // 0.98 to 1.01 times as long.  The rows of dense layers are fewer and their sums don't cancel.
 constexpr float kSplitScale = 0x1p40f, kSplitUnscale = 0x1p-80f;
 constexpr int kPieces = 3;
-constexpr int kFewTerms = 4;   // at 2 terms 2.6e-8 (with a 6-bit h, below, 3.4e-8) against 3.1e-8, at 4 2.7 (3.4) against 4.0
+// At 2 terms the split's error is 2.6e-8 (3.4e-8 with a 6-bit h) and that of fp32 products 3.1e-8, at
+// 3 2.7e-8 (3.4e-8) and 3.6e-8; four are what one step of fp32 instructions takes.
+constexpr int kFewTerms = 4;
 
 template <bool NARROW>
 __device__ __forceinline__ void split2(float x, float y, float scale, uint32_t (&o)[kPieces]) {
@@ -809,7 +811,8 @@ struct WaveGrid {
 // root mean square, or 2^-22 and 2.3e-8 where one operand's h is narrow.  h h
 // goes to acc, the five smaller products to low: next to an accumulator that one
 // large term has raised, the matrix instruction drops the last bits of every
-// small term, always the same ones for operands that repeat.  In one accumulator, column sums of (softmax - onehot) W came out
+// small term, always the same ones for operands that repeat.  In one accumulator,
+// column sums of (softmax - onehot) W came out
 // 1.8e-6 off instead of 5.6e-7.
 template <class LA, class LB, int MB, int NB>
 __device__ __forceinline__ void mma_split(floatx16 (&acc)[MB][NB], floatx16 (&low)[MB][NB],
@@ -1220,7 +1223,8 @@ template <template <int> class LAT, template <int> class LBT, bool BIAS, class F
 hipError_t dispatch_rows(const float* A, FB fb, float* c, const float* bias, int64_t M, int64_t N,
                          int64_t K, hipStream_t s) {
   const int64_t cols = (N + 63) / 64;
-  const int64_t rows = std::max<int64_t>(1, kMaxTiles / cols / 4) * 256;   // whole tiles of any shape
+  // whole tiles of any shape
+  const int64_t rows = std::max<int64_t>(1, kMaxTiles / cols / 4) * 256;
   for (int64_t m = 0; m < M; m += rows) {
     const auto fa = [=](auto& l) { l.p = A + m * K; l.ld = K; l.kdim = K; };
     const hipError_t e = dispatch_dense<LAT, LBT, BIAS>(fa, fb, c + m * N, N, bias,
